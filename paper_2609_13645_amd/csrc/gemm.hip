@@ -4,10 +4,10 @@
 // backward of each GEMM is one data-gradient and one weight-gradient
 // product): y = x W^T (both operands K-contiguous), dX = dY W (W is
 // N-contiguous) and dW += dY^T X (both operands M/N-contiguous, reduction
-// over tokens). Two pipelines share tile order, operand layouts and epilogue
+// over tokens). Three pipelines share tile order, operand layouts and epilogue
 // stores:
 //
-//  * ring_kernel (every layout; all 256 x 256 tiles): v_mfma_f32_16x16x32_bf16
+//  * ring_kernel (every layout; the large tiles): v_mfma_f32_16x16x32_bf16
 //    over a ring of four 32-deep LDS stages, one MFMA k-step per stage. The
 //    barrier that publishes stage s + 1 sits two MFMAs into stage s; after it
 //    the fragment reads of stage s + 1 and the DMA of stage s + 4 (into the
@@ -18,7 +18,9 @@
 //    wait for every outstanding DMA before each of them. The 16x16x32 shape
 //    does the work of 32x32x16 at the same rate per cycle with less power,
 //    which keeps the clock higher under load.
-//  * gemm_kernel (K-contiguous 256 x 192 and small tiles): v_mfma_f32_32x32x16
+//  * wave_kernel (every layout; 64 x 64 tiles, for products of few tiles): the
+//    waves of a workgroup split the reduction, each with a ring of its own.
+//  * gemm_kernel (K-contiguous 256 x 192 and 128 x 128): v_mfma_f32_32x32x16
 //    over a block tile BM x BN x 64 double-buffered in LDS, one barrier per
 //    k-step placed before the step's last 16-deep slice; the barrier also
 //    frees the current buffer, which is refilled at once with the step after
@@ -178,7 +180,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs& p, const f32x16_t (&a
 
 // Tile of this workgroup (tm, tn) and the group-adjusted arguments; false
 // when the workgroup has no tile (M-grouped launches over-provision).
-template <int BM, int BN, int EPI, int GROUP>
+template <int BM, int BN, int EPI, int GROUP, int LA = kMC, int LB = kMC>
 __device__ __forceinline__ bool tile_setup(GemmArgs& p, int& tm, int& tn) {
   if (GROUP == 0) {
     // ---- tile order: XCD-contiguous bands, GROUP_M rows of tiles per band ----
@@ -263,14 +265,20 @@ __device__ __forceinline__ bool tile_setup(GemmArgs& p, int& tm, int& tn) {
     // (ks = p.strideB) and stores its partial product to C + e * strideC
     const int tiles_m = (p.M + BM - 1) / BM;
     const int tiles_n = (p.N + BN - 1) / BN;
-    const int e = blockIdx.x / (tiles_m * tiles_n);
-    const int t = blockIdx.x % (tiles_m * tiles_n);
-    tm = t / tiles_n;
-    tn = t % tiles_n;
+    const int nb = gridDim.x, bid = blockIdx.x;
+    const int nb8 = nb - nb % NUM_XCD;
+    const int pid = bid < nb8 ? (bid % NUM_XCD) * (nb8 / NUM_XCD) + bid / NUM_XCD : bid;
+    const int e = pid / (tiles_m * tiles_n);
+    const int t = pid % (tiles_m * tiles_n);
+    const int in_group = GROUP_M * tiles_n;
+    const int first_m = (t / in_group) * GROUP_M;
+    const int gsize = min(tiles_m - first_m, GROUP_M);
+    tm = first_m + (t % in_group) % gsize;
+    tn = (t % in_group) / gsize;
     const long k0 = (long)e * p.strideB;
     p.K = (int)min((long)p.K - k0, p.strideB);
-    p.A += k0 * p.lda;  // both operands M/N-contiguous: k rows
-    p.B += k0 * p.ldb;
+    p.A += LA == kKC ? k0 : k0 * p.lda;
+    p.B += LB == kKC ? k0 : k0 * p.ldb;
     p.C = (char*)p.C + (long)e * p.strideC * 4;
   } else {
     // K-grouped: one (m, n) tile grid per group, reduction over the group's
@@ -310,7 +318,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 1) void gemm_kernel(GemmArgs
   __shared__ uint4 lds[2][A_ELEMS + B_ELEMS];
 
   int tm, tn;
-  if (!tile_setup<BM, BN, EPI, GROUP>(p, tm, tn)) return;
+  if (!tile_setup<BM, BN, EPI, GROUP, LA, LB>(p, tm, tn)) return;
   const int m0 = tm * BM, n0 = tn * BN;
 
   const int lane = threadIdx.x & 63;
@@ -390,7 +398,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 1) void gemm_kernel(GemmArgs
 
 // ---- ring pipeline: four 32-deep stages, 16x16x32 MFMAs ---------------------
 // Stage slot = A part then B part. K-contiguous operand: ROWS rows of four
-// 16-byte chunks (k 0..31), chunk c of row r at c ^ ((r >> 2) & 3).
+// 16-byte chunks (k 0..31), chunk c of row r at c ^ ((r >> 1) & 3).
 // M/N-contiguous operand: 32 k-rows of ROWS elements, 16-byte chunk c of
 // k-row k at c ^ ((k & 3) << 2) ^ (((k >> 3) & 1) << 1). A fragment read
 // touches k-rows {0..3} and {8..11} (or their +4 / +16 shifts) in one
@@ -414,11 +422,19 @@ struct RingPart {
 __device__ __forceinline__ int kc_swz(int row) { return (row >> 1) & 3; }
 __device__ __forceinline__ int kc4(int row, int c) { return row * 4 + (c ^ kc_swz(row)); }
 
-__device__ __forceinline__ int mc_swz(int k) { return ((k & 3) << 2) ^ (((k >> 3) & 1) << 1); }
+// M/N-contiguous stage of ROWS elements per k-row (see above). 64-element rows
+// are 128 bytes, two to a 256-byte bank window: the four k-rows of one parity
+// (k = 0, 2, 8, 10 and their shifts) take the four 32-byte pieces of a row.
+template <int ROWS>
+__device__ __forceinline__ int mc_swz(int k) {
+  static_assert(ROWS >= 64, "the swizzle needs at least eight chunks per k-row");
+  return ROWS >= 128 ? ((k & 3) << 2) ^ (((k >> 3) & 1) << 1)
+                     : (((k >> 1) & 1) << 1) | (((k >> 3) & 1) << 2);
+}
 
 template <int ROWS>
 __device__ __forceinline__ int mc_ring_elem(int k, int m) {
-  return k * ROWS + (((m >> 3) ^ mc_swz(k)) << 3) + (m & 7);
+  return k * ROWS + (((m >> 3) ^ mc_swz<ROWS>(k)) << 3) + (m & 7);
 }
 
 __device__ __forceinline__ uint32_t lds_addr(const void* ptr) {
@@ -441,10 +457,9 @@ __device__ __forceinline__ void ring_dma(int i, const bf16_t* __restrict__ src, 
   } else {
     constexpr int LPR = ROWS / 8;  // lanes per k-row
     constexpr int RPI = 64 / LPR;  // k-rows per instruction
-    static_assert(LPR >= 16, "the swizzle needs at least 16 chunks per k-row");
     const __amdgpu_buffer_rsrc_t r = rsrc(src + (long)k0 * ld + row0);
     const int k = blk * RPI + lane / LPR;
-    const int c = (lane % LPR) ^ mc_swz(k);
+    const int c = (lane % LPR) ^ mc_swz<ROWS>(k);
     const bool ok = (k0 + k < K) && (row0 + c * 8 < rows_lim);
     const uint32_t off = ok ? (uint32_t)(((long)k * ld + c * 8) * 2) : kOOB;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)(part + blk * 64), 16, off, 0, 0, 0);
@@ -708,7 +723,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 1) void ring_kernel(GemmArgs
   __shared__ uint4 lds[4 * SLOT];
 
   int tm, tn;
-  if (!tile_setup<BM, BN, EPI, GROUP>(p, tm, tn)) return;
+  if (!tile_setup<BM, BN, EPI, GROUP, LA, LB>(p, tm, tn)) return;
   const int m0 = tm * BM, n0 = tn * BN;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -803,16 +818,187 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 1) void ring_kernel(GemmArgs
   }
 }
 
-// Operands contiguous along M / N and full 256 x 256 tiles run on the ring
-// pipeline; the remaining K-contiguous tiles (256 x 192 and the small ones)
-// on the double-buffered one.
+// ---- small products: the reduction split over the waves of a workgroup ------
+// A product of few output tiles leaves most CUs idle on large tiles, and on
+// small ones each workgroup is a chain of short k-steps whose latency (DMA,
+// LDS read, barrier) nothing hides. Here every wave owns the whole BM x BN
+// tile and takes the 32-deep stages wave, wave + NW, ...: each streams its
+// stages through a ring of its own (R slots of LDS), so the loop has no
+// barrier, the waves of a SIMD hide each other's latency, and the serial chain
+// is NW times shorter. At the end the NW partial tiles are added through LDS
+// in wave order (deterministic) and each thread stores eight consecutive n.
+// Four waves and two slots (64 KB of LDS): two workgroups share a CU; eight
+// waves, or four with four slots, measured the same or slower (1000 x 1024 x
+// 3072 data gradient: 12.7 us, 13.1, 13.2; 128 x 128 tiles 40.7). Bound by the
+// latency of the chain up to one workgroup per CU (128 x 256 x 1376: 6.9 us
+// against 21 on 128 x 128 tiles), beyond that by the L2 -> LDS stream of the
+// small tiles (2048^3: 30 us, 128 x 128 tiles 25-26). Ordinary stores: the next
+// kernel reads a result this small from L2.
+template <int EPI>
+__device__ __forceinline__ void store8_cached(const GemmArgs& p, int m, int n, float* x) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) x[e] *= p.alpha;
+  const bool full = n + 7 < p.N;
+  if (EPI == kStoreBF16 || EPI == kResidBF16) {
+    bf16_t* C = reinterpret_cast<bf16_t*>(p.C) + (long)m * p.ldc + n;
+    const bf16_t* R = p.R + (long)m * p.ldr + n;
+    if (full) {
+      if (EPI == kResidBF16) {
+        float r[8];
+        unpack8(*reinterpret_cast<const uint4*>(R), r);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] += r[e];
+      }
+      *reinterpret_cast<uint4*>(C) = pack8(x);
+    } else {
+      for (int e = 0; e < 8; ++e)
+        if (n + e < p.N) C[e] = f2bf(EPI == kResidBF16 ? x[e] + bf2f(R[e]) : x[e]);
+    }
+  } else {
+    float* C = reinterpret_cast<float*>(p.C) + (long)m * p.ldc + n;
+    if (full) {
+      float4* C4 = reinterpret_cast<float4*>(C);
+      float4 a = make_float4(x[0], x[1], x[2], x[3]), b = make_float4(x[4], x[5], x[6], x[7]);
+      if (EPI == kAccF32) {
+        const float4 c = C4[0], d = C4[1];
+        a = make_float4(a.x + c.x, a.y + c.y, a.z + c.z, a.w + c.w);
+        b = make_float4(b.x + d.x, b.y + d.y, b.z + d.z, b.w + d.w);
+      }
+      C4[0] = a;
+      C4[1] = b;
+    } else {
+      for (int e = 0; e < 8; ++e)
+        if (n + e < p.N) C[e] = (EPI == kAccF32 ? C[e] : 0.0f) + x[e];
+    }
+  }
+}
+
+template <int BM, int BN, int NW, int R, int LA, int LB, int EPI, int GROUP>
+__global__ __launch_bounds__(NW * 64) void wave_kernel(GemmArgs p) {
+  constexpr int FM = BM / 16, FN = BN / 16, NM = FM * FN;
+  constexpr int AE = RingPart<BM, 1>::ELEMS, BE = RingPart<BN, 1>::ELEMS, SLOT = AE + BE;
+  constexpr int DA = RingPart<BM, 1>::PER, DB = RingPart<BN, 1>::PER, D = DA + DB;
+  constexpr int CPR = BN / 4;       // fp32 chunks of 16 bytes per tile row
+  constexpr int RED = BM * CPR;     // chunks of one wave's partial tile
+  constexpr int LDS = NW * (R * SLOT > RED ? R * SLOT : RED);
+  static_assert(R * D < 64 && LDS * 16 <= 160 * 1024, "ring depth");
+  __shared__ uint4 lds[LDS];
+
+  int tm, tn;
+  if (!tile_setup<BM, BN, EPI, GROUP, LA, LB>(p, tm, tn)) return;
+  const int m0 = tm * BM, n0 = tn * BN;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint4* ring = lds + wave * R * SLOT;
+
+  f32x4_t acc[FN][FM];
+#pragma unroll
+  for (int i = 0; i < FN; ++i)
+#pragma unroll
+    for (int j = 0; j < FM; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.0f;
+  const int nst = (p.K + SK - 1) / SK;
+  const int cnt = nst > wave ? (nst - wave + NW - 1) / NW : 0;
+
+  // stage i of this wave (stage wave + i NW of the tile) into slot u; zeros
+  // past K
+  auto dma = [&](int i, int u) __attribute__((always_inline)) {
+    const int k0 = (wave + i * NW) * SK;
+    uint4* slot = ring + u * SLOT;
+#pragma unroll
+    for (int d = 0; d < DA; ++d)
+      ring_dma<BM, 1, LA>(d, p.A, p.lda, m0, p.M, k0, p.K, slot, 0, lane);
+#pragma unroll
+    for (int d = 0; d < DB; ++d)
+      ring_dma<BN, 1, LB>(d, p.B, p.ldb, n0, p.N, k0, p.K, slot + AE, 0, lane);
+  };
+  auto read = [&](bf16x8_t (&fa)[FN], bf16x8_t (&fb)[FM], int u) __attribute__((always_inline)) {
+    const uint4* slot = ring + u * SLOT;
+#pragma unroll
+    for (int i = 0; i < FN; ++i) fa[i] = ring_frag<LB, BN>(slot + AE, i * 16, lane);
+#pragma unroll
+    for (int j = 0; j < FM; ++j) fb[j] = ring_frag<LA, BM>(slot, j * 16, lane);
+  };
+
+  if (cnt > 0) {
+    // the loop runs R stages at a time, so that slots and fragment buffers are
+    // fixed; stages past the last are zeros. Each step: the stage's fragments
+    // (read during the previous step) arrive, its slot takes the stage R ahead,
+    // half of its MFMAs, then the next stage's DMA has landed and its
+    // fragments are read under the other half.
+    static_assert(R % 2 == 0, "fragment buffers alternate");
+#pragma unroll
+    for (int u = 0; u < R; ++u) dma(u, u);
+    bf16x8_t fa[2][FN], fb[2][FM];
+    wait_dma<(R - 1) * D>();
+    read(fa[0], fb[0], 0);
+    for (int i = 0; i < cnt; i += R) {
+#pragma unroll
+      for (int u = 0; u < R; ++u) {
+        constexpr int H = NM / 2;
+        const int h = u & 1;
+        ring_fence<FN, FM>(fa[h], fb[h]);
+        __builtin_amdgcn_sched_barrier(0);
+        dma(i + u + R, u);
+#pragma unroll
+        for (int q = 0; q < NM; ++q) {
+          if (q == H) {
+            __builtin_amdgcn_sched_barrier(0);
+            wait_dma<(R - 1) * D>();
+            read(fa[h ^ 1], fb[h ^ 1], (u + 1) % R);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          acc[q / FM][q % FM] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              fa[h][q / FM], fb[h][q % FM], acc[q / FM][q % FM], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    // the (unused) last reads and DMA land before their registers and slots
+    // are reused
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    ring_fence<FN, FM>(fa[0], fb[0]);
+  }
+  __syncthreads();
+  // partial tiles to LDS: row m of wave w holds its chunks XOR-ed with m % 16
+  // (16 rows of one chunk, and the chunks of two rows, cover all banks)
+  f32x4_t* red = reinterpret_cast<f32x4_t*>(lds);
+  constexpr int XM = CPR >= 16 ? 15 : CPR - 1;
+#pragma unroll
+  for (int i = 0; i < FN; ++i)
+#pragma unroll
+    for (int j = 0; j < FM; ++j) {
+      const int m = j * 16 + (lane & 15), c = i * 4 + (lane >> 4);
+      red[wave * RED + m * CPR + (c ^ (m & XM))] = acc[i][j];
+    }
+  __syncthreads();
+  constexpr int ITEMS = BM * BN / 8;
+  for (int t = threadIdx.x; t < ITEMS; t += NW * 64) {
+    const int m = t / (BN / 8), c = (t % (BN / 8)) * 2;
+    const f32x4_t* r = red + m * CPR;
+    f32x4_t a = r[c ^ (m & XM)], b = r[(c + 1) ^ (m & XM)];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) {
+      a += r[w * RED + (c ^ (m & XM))];
+      b += r[w * RED + ((c + 1) ^ (m & XM))];
+    }
+    float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+    if (m0 + m < p.M && n0 + c * 4 < p.N) store8_cached<EPI>(p, m0 + m, n0 + c * 4, x);
+  }
+}
+
+// The ring pipeline runs every tile except the K-contiguous 256 x 192 and
+// 128 x 128 ones, which run on the double-buffered kernel.
 template <int BM, int BN, int WAVES_M, int WAVES_N, int LA, int LB, int EPI, int GROUP>
 void launch_kernel(const GemmArgs& a, long grid, hipStream_t s) {
-  if constexpr (LA == kMC || LB == kMC || (BM == 256 && BN == 256) || GROUP == 4)
-    hipLaunchKernelGGL((ring_kernel<BM, BN, WAVES_M, WAVES_N, LA, LB, EPI, GROUP>),
+  constexpr bool kBuffered = LA == kKC && LB == kKC && GROUP == 0 &&
+                             ((BM == 256 && BN == 192) || (BM == 128 && BN == 128));
+  if constexpr (kBuffered)
+    hipLaunchKernelGGL((gemm_kernel<BM, BN, WAVES_M, WAVES_N, LA, LB, EPI, GROUP>),
                        dim3((unsigned)grid), dim3(WAVES_M * WAVES_N * 64), 0, s, a);
   else
-    hipLaunchKernelGGL((gemm_kernel<BM, BN, WAVES_M, WAVES_N, LA, LB, EPI, GROUP>),
+    hipLaunchKernelGGL((ring_kernel<BM, BN, WAVES_M, WAVES_N, LA, LB, EPI, GROUP>),
                        dim3((unsigned)grid), dim3(WAVES_M * WAVES_N * 64), 0, s, a);
 }
 
@@ -866,11 +1052,79 @@ __global__ __launch_bounds__(256) void splitk_reduce_k(const float* __restrict__
 
 constexpr int kCUs = 256;
 
+// ---- choice of the tile ------------------------------------------------------
+// Four tile shapes cover everything below a chip full of 256 x 256 tiles:
+// 256 x 256, 128 x 256 and 128 x 128 with the waves side by side in the tile,
+// 64 x 64 with the waves splitting the reduction (wave_kernel). None wins
+// everywhere: a large tile reads the least per FLOP and leaves CUs idle when
+// there are few of them, a small one the reverse. The choice is the smallest
+// estimate of
+//   fixed + round * (rounds - 1) + K * (per_k + full_k * share of CUs busy) * rounds
+// microseconds, rounds counted over the tiles resident at once (`slots`: two
+// workgroups of the four-wave tiles share a CU; a last round that gives every
+// CU at most one of them costs `half`). The constants are a fit (10-15 % rms)
+// to 130 products, M, N in 64..16384, K in 64..16384, all layouts, timed on
+// every tile: the pick is on average 2 % slower than the fastest tile, and
+// 1.47 times as fast as one threshold on the number of tiles (256 x 256 from
+// 256 tiles, then 256 x 128, else 128 x 128). E.g. (M, N, K) = (1000, 1024,
+// 3072), data gradient: 12.7 us on 64 x 64, 40.7 on 128 x 128; (2048, 2048,
+// 3072): 38 on 128 x 256, 41 on 128 x 128, 60 on 256 x 256.
+enum Tile { kT256, kT128x256, kT128, kT64, kTiles };
+constexpr int kTileM[kTiles] = {256, 128, 128, 64}, kTileN[kTiles] = {256, 256, 128, 64};
+struct TileCost {
+  double fixed, per_k, full_k;
+};
+constexpr int kSlots[kTiles] = {256, 256, 512, 512};
+constexpr double kHalfRound[kTiles] = {1.0, 1.0, 0.55, 0.52}, kRound[kTiles] = {8.0, 5.0, 6.0, 1.7};
+// [layout: (KC, KC), (KC, MC), (MC, MC)][tile]
+constexpr TileCost kCost[3][kTiles] = {
+    {{10.0, .0150, .0120}, {6.0, .0092, .0068}, {4.3, .0110, .0070}, {3.7, .0037, .0040}},
+    {{10.0, .0155, .0100}, {6.5, .0093, .0055}, {6.0, .0175, .0010}, {3.7, .0043, .0042}},
+    {{10.5, .0168, .0094}, {6.5, .0108, .0040}, {4.5, .0150, .0010}, {5.0, .0066, .0024}}};
+
+long tile_count(int t, long M, long N) {
+  return ((M + kTileM[t] - 1) / kTileM[t]) * ((N + kTileN[t] - 1) / kTileN[t]);
+}
+
+double tile_cost(int layout, int t, long tiles, long K) {
+  const TileCost& c = kCost[layout][t];
+  const long full = tiles / kSlots[t], rem = tiles % kSlots[t];
+  const double part = rem == 0 ? 0.0 : (rem <= kCUs ? kHalfRound[t] : 1.0);
+  const double busy = (double)(tiles < kCUs ? tiles : kCUs) / kCUs;
+  return c.fixed + kRound[t] * (double)(full + (rem > 0) - 1) +
+         (double)K * (c.per_k + c.full_k * busy) * ((double)full + part);
+}
+
+Tile pick_tile(int layout, long M, long N, long K) {
+  int best = kT256;
+  double cost = tile_cost(layout, kT256, tile_count(kT256, M, N), K);
+  for (int t = kT256 + 1; t < kTiles; ++t) {
+    const double c = tile_cost(layout, t, tile_count(t, M, N), K);
+    if (c < cost) {
+      cost = c;
+      best = t;
+    }
+  }
+  return (Tile)best;
+}
+
+template <int LA, int LB, int EPI>
+hipError_t launch_wave(const GemmArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL((wave_kernel<64, 64, 4, 2, LA, LB, EPI, 0>),
+                     dim3((unsigned)tile_count(kT64, a.M, a.N)), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
 template <int LA, int LB, int EPI>
 hipError_t dispatch_tiles(const GemmArgs& a, hipStream_t s) {
-  // Large tiles once they fill the chip, smaller ones for small problems.
-  const long big = (long)((a.M + 255) / 256) * ((a.N + 255) / 256);
-  const long mid = (long)((a.M + 255) / 256) * ((a.N + 127) / 128);
+  const long big = tile_count(kT256, a.M, a.N);
+  // from a chip full of 256 x 256 tiles up no other tile is faster (8192 x
+  // 1536 x 1536 has 192: 36.9 us, 128 x 128 46.8, 128 x 256 50.1)
+  const Tile t = big >= kCUs ? kT256
+                             : pick_tile(LA == kMC ? 2 : (LB == kMC ? 1 : 0), a.M, a.N, a.K);
+  if (t == kT64) return launch_wave<LA, LB, EPI>(a, s);
+  if (t == kT128) return launch<128, 128, 2, 2, LA, LB, EPI>(a, s);
+  if (t == kT128x256) return launch<128, 256, 2, 4, LA, LB, EPI>(a, s);
   if constexpr (LA == kKC && LB == kKC) {
     const long tail = big % kCUs;
     if (big > kCUs && tail <= kCUs / 2 && tail > 0) {
@@ -897,16 +1151,12 @@ hipError_t dispatch_tiles(const GemmArgs& a, hipStream_t s) {
       if (c192 < c256) return launch<256, 192, 4, 2, LA, LB, EPI>(a, s);
     }
   }
-  // 8 waves of 64 x 128 (two per SIMD)
-  if (big >= 256) {
-    // 128 x 64 wave tiles (2 x 4 waves): in a data gradient (B M/N-contiguous,
-    // read with the slower transposing reads) they put the transposing reads
-    // on the narrow side of the wave tile, half as many per stage as with
-    // 64 x 128; the other products measured no slower (slightly faster)
-    return launch<256, 256, 2, 4, LA, LB, EPI>(a, s);
-  }
-  if (mid >= 256) return launch<256, 128, 2, 2, LA, LB, EPI>(a, s);
-  return launch<128, 128, 2, 2, LA, LB, EPI>(a, s);
+  // 128 x 64 wave tiles (2 x 4 waves, two per SIMD): in a data gradient (B
+  // M/N-contiguous, read with the slower transposing reads) they put the
+  // transposing reads on the narrow side of the wave tile, half as many per
+  // stage as with 64 x 128; the other products measured no slower (slightly
+  // faster)
+  return launch<256, 256, 2, 4, LA, LB, EPI>(a, s);
 }
 
 }  // namespace

@@ -146,6 +146,49 @@ def test_gemm_split_last_round_integer_exact(M, N, K, epi):
     assert np.array_equal(got, want)
 
 
+# below a chip full of 256 x 256 tiles: 64 x 64 with the reduction split over
+# the waves (fewer stages than waves, one ragged stage, ragged tiles in both
+# directions), 128 x 128, 128 x 256, 256 x 256
+@pytest.mark.parametrize("la,lb,epi", COMBOS)
+@pytest.mark.parametrize("M,N,K", [(64, 64, 32), (72, 56, 104), (1000, 264, 2056), (2056, 1032, 296),
+                                   (3080, 1032, 1000), (2056, 2040, 2072), (3840, 4088, 1032)])
+def test_gemm_tile_choice_integer_exact(la, lb, epi, M, N, K):
+    banner(f"gemm int tile choice la={la} lb={lb} epi={epi} M={M} N={N} K={K}")
+    got, ref = run_gemm(la, lb, epi, M, N, K, seed=M + N + K + epi)
+    want = (fi.bf16_bits_to_f64(fi.to_bf16_bits(ref.astype(np.float32)))
+            if epi in (STORE_BF16, RESID_BF16) else ref)
+    assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("M,N,K", [(100, 77, 72), (129, 1031, 520)])
+@pytest.mark.parametrize("epi", [STORE_BF16, RESID_BF16, ACC_F32, STORE_F32])
+def test_gemm_odd_rows_and_columns_integer_exact(epi, M, N, K):
+    """K-contiguous operands take any M and N: the last piece of a row ends
+    inside its eight columns and nothing is written past it (C has a leading
+    dimension of a multiple of eight)."""
+    import torch
+    from paper_2609_13645_amd import _lib
+    banner(f"gemm int odd M={M} N={N} K={K} epi={epi}")
+    rng = np.random.default_rng(M * N + epi)
+    A = rng.integers(-4, 5, size=(M, K)).astype(np.float32)
+    B = rng.integers(-4, 5, size=(N, K)).astype(np.float32)
+    ld = (N + 7) // 8 * 8
+    bf = epi in (STORE_BF16, RESID_BF16)
+    init = rng.integers(-8, 9, size=(M, ld)).astype(np.float32)
+    C = torch.from_numpy(init).cuda()
+    C = C.bfloat16() if bf else C
+    R = dev_bf16(fi.to_bf16_bits(init)) if epi == RESID_BF16 else None
+    _lib.forge_gemm(KC, KC, epi, dev_bf16(fi.to_bf16_bits(A)), dev_bf16(fi.to_bf16_bits(B)), C, R,
+                    M, N, K, K, K, ld, ld if R is not None else 0)
+    torch.cuda.synchronize()
+    want = init.astype(np.float64)
+    prod = A.astype(np.float64) @ B.astype(np.float64).T
+    want[:, :N] = prod + (want[:, :N] if epi in (RESID_BF16, ACC_F32) else 0.0)
+    if bf:
+        want = fi.bf16_bits_to_f64(fi.to_bf16_bits(want.astype(np.float32)))
+    assert np.array_equal(host_f64(C), want)
+
+
 def test_gemm_zero_k_and_empty():
     banner("gemm K=0 / empty")
     got, ref = run_gemm(KC, KC, ACC_F32, 64, 64, 0)
