@@ -192,7 +192,9 @@ forge_status forge_layer_saved_bytes(const forge_layer_cfg* cfg, size_t* bytes);
  * Host only. The contents need not be preserved between calls. Includes the
  * attention backward's dS scratch: batch * n_heads * 4096 * t (t + 1) / 2
  * bf16 for t = ceil(seq / 64) 64-key tiles (the causal half of each head's
- * seq x seq score gradient; 545 MB at 32 heads and seq 4096). */
+ * seq x seq score gradient; 545 MB at 32 heads and seq 4096), and, for layers
+ * whose products have few output tiles, up to 2 x 64 MB of fp32 partial
+ * products. */
 forge_status forge_layer_workspace_bytes(const forge_layer_cfg* cfg, size_t* bytes);
 
 /* Items of a MoE layer's saved buffer that forge_layer_saved_item locates:
@@ -293,7 +295,9 @@ forge_status forge_swiglu_bwd(const forge_bf16* gu, const forge_bf16* da, forge_
  * For a MoE layer the FFN branch is h1 + sum_j gate_j FFN_{e_j}(b) instead.
  * saved: forge_layer_saved_bytes bytes, written here, read by the backward.
  * workspace: forge_layer_workspace_bytes bytes of scratch (may be NULL for a
- * dense layer without recompute_attn).
+ * dense layer without recompute_attn; products of few output tiles then do
+ * not split their reduction, so their sums are ordered differently and small
+ * layers run slower).
  * aux_loss: device fp32 scalar, MoE only: += the layer's load-balance loss;
  * may be NULL (the loss is then not reported; the backward still includes
  * its gradient).
@@ -332,7 +336,8 @@ typedef struct {
   float logit_scale;
 } forge_head_cfg;
 
-/* Scratch bytes for forge_loss_fwd_bwd (holds the [T, V] bf16 logits). */
+/* Scratch bytes for forge_loss_fwd_bwd (holds the [T, V] bf16 logits, and up
+ * to 64 MB of fp32 partial products). */
 forge_status forge_loss_workspace_bytes(const forge_head_cfg* cfg, size_t* bytes);
 
 /*

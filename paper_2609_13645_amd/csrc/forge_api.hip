@@ -195,9 +195,28 @@ Saved saved_layout(const forge_layer_cfg& c) {
 // ---- workspace -------------------------------------------------------------
 struct Work {
   size_t dA, dgu, db, dh1, dO, delta, ds, dqkv, da, dg, o, lse;
-  size_t logits, blk, colsum, dys, dxs, dgate, dl, dbs, wpart;  // MoE
+  size_t logits, blk, colsum, dys, dxs, dgate, dl, dbs;  // MoE
   size_t qk_dg, h1s, dA_s, dgu_s, db1;  // QK-Norm; shared expert
+  // partial products of split reductions: of the forward and the data
+  // gradients (the caller's stream), and of the weight gradients (which may
+  // run on the side stream at the same time)
+  size_t part, wpart, part_bytes, wpart_bytes;
   size_t total;
+};
+
+// Scratch of split products: the largest of those that share it.
+struct SplitScratch {
+  size_t bytes = 0;
+  void add(forge::GemmLayout la, forge::GemmLayout lb, long M, long N, long K) {
+    bytes = std::max(bytes, forge::gemm_split_bytes(la, lb, M, N, K));
+  }
+  // the three products of a projection [n_out, n_in] over T rows: forward and
+  // data gradient here, weight gradient in w
+  void projection(SplitScratch& w, long T, long n_out, long n_in) {
+    add(forge::kKC, forge::kKC, T, n_out, n_in);
+    add(forge::kKC, forge::kMC, T, n_in, n_out);
+    w.add(forge::kMC, forge::kMC, n_out, n_in, T);
+  }
 };
 
 forge::AttnArgs attn_args(const Dims& d, const uint16_t* qkv);
@@ -221,8 +240,6 @@ Work work_layout(const forge_layer_cfg& c) {
     w.dgate = take(d.R * 4);
     w.dl = take(d.T * d.E * 2);
     w.dbs = take(d.T * d.h * 2);
-    const int rs = forge::splitk_splits((int)d.E, (int)d.h, (int)d.T);
-    w.wpart = rs > 1 ? take((size_t)rs * d.E * d.h * 4) : 0;
     if (d.fs) {
       w.h1s = take(d.T * d.h * 2);
       w.dA_s = take(d.T * d.fs * 2);
@@ -244,6 +261,23 @@ Work work_layout(const forge_layer_cfg& c) {
   const bool rec = c.recompute_attn != 0;
   w.o = rec ? take(d.T * d.hq * 2) : 0;
   w.lse = rec ? take(d.B * d.nh * d.S * 4) : 0;
+  SplitScratch here, side;
+  here.projection(side, d.T, d.qkv, d.h);
+  here.projection(side, d.T, d.h, d.hq);
+  if (d.E == 0) {
+    here.projection(side, d.T, 2 * d.f, d.h);
+    here.projection(side, d.T, d.h, d.f);
+  } else {
+    here.projection(here, d.T, d.E, d.h);  // (the router's weight gradient: caller's stream)
+    if (d.fs) {
+      here.projection(side, d.T, 2 * d.fs, d.h);
+      here.projection(side, d.T, d.h, d.fs);
+    }
+  }
+  w.part_bytes = here.bytes;
+  w.wpart_bytes = side.bytes;
+  w.part = take(here.bytes);
+  w.wpart = take(side.bytes);
   w.total = off;
   return w;
 }
@@ -273,6 +307,25 @@ GemmArgs gargs(const void* A, long lda, const void* B, long ldb, void* C, long l
   g.ldr = ldr;
   return g;
 }
+
+// The layer's products with the scratch of split reductions: on the caller's
+// stream (none without a workspace, which a dense forward may leave out or,
+// since it needs no other scratch, pass at any alignment), or a weight
+// gradient's.
+struct Products {
+  void* ws;
+  const Work& wk;
+  hipError_t here(forge::GemmLayout la, forge::GemmLayout lb, forge::GemmEpilogue epi,
+                  const GemmArgs& a, hipStream_t s) const {
+    const bool use = ws != nullptr && aligned16(ws);
+    float* part = use ? reinterpret_cast<float*>(static_cast<char*>(ws) + wk.part) : nullptr;
+    return forge::gemm(la, lb, epi, a, s, part, part ? wk.part_bytes : 0);
+  }
+  hipError_t wgrad(forge::GemmEpilogue epi, const GemmArgs& a, hipStream_t s) const {
+    return forge::gemm(forge::kMC, forge::kMC, epi, a, s,
+                       reinterpret_cast<float*>(static_cast<char*>(ws) + wk.wpart), wk.wpart_bytes);
+  }
+};
 
 // the same product with every epilogue value multiplied by alpha (a residual
 // branch's scale)
@@ -369,10 +422,11 @@ forge_status check_grads(const forge_layer_cfg& c, const forge_layer_grads* g) {
 forge_status attn_block_fwd(const forge_layer_cfg& c, const Dims& d,
                             const forge_layer_weights* w, const uint16_t* x, uint16_t* a,
                             float* rstd1, uint16_t* qkv, uint16_t* o, float* lse, uint16_t* h1,
-                            uint16_t* qk_raw, float* rstd_qk, hipStream_t s) {
+                            uint16_t* qk_raw, float* rstd_qk, const Products& gemm,
+                            hipStream_t s) {
   FORGE_HIP(forge::rmsnorm_fwd(x, w->attn_norm, a, rstd1, (int)d.T, (int)d.h, c.rms_eps, s));
-  FORGE_HIP(forge::gemm(forge::kKC, forge::kKC, forge::kStoreBF16,
-                        gargs(a, d.h, w->w_qkv, d.h, qkv, d.qkv, d.T, d.qkv, d.h), s));
+  FORGE_HIP(gemm.here(forge::kKC, forge::kKC, forge::kStoreBF16,
+                      gargs(a, d.h, w->w_qkv, d.h, qkv, d.qkv, d.T, d.qkv, d.h), s));
   if (d.qkn)
     FORGE_HIP(forge::qknorm_rope_fwd(qkv, d.qkv, qk_raw, rstd_qk, w->q_norm, w->k_norm,
                                      w->rope_cos, w->rope_sin, w->positions, (int)d.T, (int)d.S,
@@ -381,9 +435,9 @@ forge_status attn_block_fwd(const forge_layer_cfg& c, const Dims& d,
     FORGE_HIP(forge::rope_apply(qkv, d.qkv, w->rope_cos, w->rope_sin, w->positions, (int)d.T,
                                 (int)d.S, (int)(d.nh + d.nkv), (int)d.d, false, s));
   FORGE_HIP(forge::attn_fwd(attn_args(d, qkv), o, lse, s));
-  FORGE_HIP(forge::gemm(forge::kKC, forge::kKC, forge::kResidBF16,
-                        scaled(gargs(o, d.hq, w->w_o, d.hq, h1, d.h, d.T, d.h, d.hq, x, d.h), d.bs),
-                        s));
+  FORGE_HIP(gemm.here(forge::kKC, forge::kKC, forge::kResidBF16,
+                      scaled(gargs(o, d.hq, w->w_o, d.hq, h1, d.h, d.T, d.h, d.hq, x, d.h), d.bs),
+                      s));
   return FORGE_OK;
 }
 
@@ -519,16 +573,16 @@ forge_status attn_block_bwd(const forge_layer_cfg& c, const Dims& d,
   float* dgp = at<float>(workspace, wk.dg);
   const int nblk = forge::rmsnorm_bwd_blocks((int)d.T);
   const forge::AttnArgs aa = attn_args(d, qkv);
+  const Products gemm{workspace, wk};
   (void)c;
   // weight gradients go to the side stream when there is one (dh1 and o
   // exist: fork now; dqkv after the RoPE backward: fork again)
   hipStream_t ws = side ? side->stream : s;
   if (side) FORGE_HIP(link(s, ws, side->ev[2]));
-  FORGE_HIP(forge::gemm(forge::kMC, forge::kMC, wgrad_epi(g),
-                        scaled(gargs(dh1, d.h, o, d.hq, g->d_w_o, d.hq, d.h, d.hq, d.T), d.bs),
-                        ws));
-  FORGE_HIP(forge::gemm(forge::kKC, forge::kMC, forge::kStoreBF16,
-                        scaled(gargs(dh1, d.h, w->w_o, d.hq, dO, d.hq, d.T, d.hq, d.h), d.bs), s));
+  FORGE_HIP(gemm.wgrad(
+      wgrad_epi(g), scaled(gargs(dh1, d.h, o, d.hq, g->d_w_o, d.hq, d.h, d.hq, d.T), d.bs), ws));
+  FORGE_HIP(gemm.here(forge::kKC, forge::kMC, forge::kStoreBF16,
+                      scaled(gargs(dh1, d.h, w->w_o, d.hq, dO, d.hq, d.T, d.hq, d.h), d.bs), s));
   if (opt) FORGE_HIP(opt_update(opt, s, ws, opt->o->w_o, g->d_w_o, d.h * d.hq));
   FORGE_HIP(forge::attn_bwd(aa, o, dO, lse, delta, at<uint16_t>(workspace, wk.ds), dqkv,
                              dqkv + d.hq, dqkv + d.hq + d.hkv, d.qkv, s));
@@ -549,10 +603,10 @@ forge_status attn_block_bwd(const forge_layer_cfg& c, const Dims& d,
                                 (int)d.S, (int)(d.nh + d.nkv), (int)d.d, true, s));
   }
   if (side) FORGE_HIP(link(s, ws, side->ev[3]));
-  FORGE_HIP(forge::gemm(forge::kMC, forge::kMC, wgrad_epi(g),
-                        gargs(dqkv, d.qkv, a, d.h, g->d_w_qkv, d.h, d.qkv, d.h, d.T), ws));
-  FORGE_HIP(forge::gemm(forge::kKC, forge::kMC, forge::kStoreBF16,
-                        gargs(dqkv, d.qkv, w->w_qkv, d.h, da, d.h, d.T, d.h, d.qkv), s));
+  FORGE_HIP(gemm.wgrad(wgrad_epi(g),
+                       gargs(dqkv, d.qkv, a, d.h, g->d_w_qkv, d.h, d.qkv, d.h, d.T), ws));
+  FORGE_HIP(gemm.here(forge::kKC, forge::kMC, forge::kStoreBF16,
+                      gargs(dqkv, d.qkv, w->w_qkv, d.h, da, d.h, d.T, d.h, d.qkv), s));
   if (opt) FORGE_HIP(opt_update(opt, s, ws, opt->o->w_qkv, g->d_w_qkv, d.qkv * d.h));
   // d_in may alias the layer's upstream gradient, which a side-stream
   // product may still be reading: wait for that product first
@@ -585,8 +639,9 @@ forge_status moe_ffn_fwd(const forge_layer_cfg& c, const Dims& d, const forge_la
   uint16_t* act = at<uint16_t>(saved, sv.act);
   uint16_t* ys = at<uint16_t>(saved, sv.ys);
   const int T = (int)d.T, E = (int)d.E, k = (int)d.k;
-  FORGE_HIP(forge::gemm(forge::kKC, forge::kKC, forge::kStoreF32,
-                        gargs(bn, d.h, w->w_router, d.h, logits, d.E, d.T, d.E, d.h), s));
+  const Products gemm{workspace, wk};
+  FORGE_HIP(gemm.here(forge::kKC, forge::kKC, forge::kStoreF32,
+                      gargs(bn, d.h, w->w_router, d.h, logits, d.E, d.T, d.E, d.h), s));
   FORGE_HIP(forge::moe_route(logits, T, E, k, idx, gates, probs, s));
   FORGE_HIP(forge::moe_sort(idx, T, E, k, at<int32_t>(workspace, wk.blk), counts, offsets, perm,
                             pos_of, s));
@@ -607,13 +662,13 @@ forge_status moe_ffn_fwd(const forge_layer_cfg& c, const Dims& d, const forge_la
     uint16_t* gu_s = at<uint16_t>(saved, sv.gu_s);
     uint16_t* act_s = at<uint16_t>(saved, sv.act_s);
     uint16_t* h1s = at<uint16_t>(workspace, wk.h1s);
-    FORGE_HIP(forge::gemm(forge::kKC, forge::kKC, forge::kStoreBF16,
-                          gargs(bn, d.h, w->w_gate_up_s, d.h, gu_s, 2 * d.fs, d.T, 2 * d.fs, d.h),
-                          s));
+    FORGE_HIP(gemm.here(forge::kKC, forge::kKC, forge::kStoreBF16,
+                        gargs(bn, d.h, w->w_gate_up_s, d.h, gu_s, 2 * d.fs, d.T, 2 * d.fs, d.h),
+                        s));
     FORGE_HIP(forge::swiglu_fwd(gu_s, act_s, (int)d.T, (int)d.fs, s));
-    FORGE_HIP(forge::gemm(forge::kKC, forge::kKC, forge::kResidBF16,
-                          scaled(gargs(act_s, d.fs, w->w_down_s, d.fs, h1s, d.h, d.T, d.h, d.fs,
-                                       h1, d.h), d.bs), s));
+    FORGE_HIP(gemm.here(forge::kKC, forge::kKC, forge::kResidBF16,
+                        scaled(gargs(act_s, d.fs, w->w_down_s, d.fs, h1s, d.h, d.T, d.h, d.fs,
+                                     h1, d.h), d.bs), s));
     resid = h1s;
   }
   FORGE_HIP(forge::moe_combine(ys, gates, pos_of, resid, d.T, (int)d.h, k, d.bs, out, s));
@@ -647,6 +702,7 @@ forge_status moe_ffn_bwd(const forge_layer_cfg& c, const Dims& d, const forge_la
   uint16_t* dl = at<uint16_t>(workspace, wk.dl);
   uint16_t* dbs = at<uint16_t>(workspace, wk.dbs);
   const int T = (int)d.T, E = (int)d.E, k = (int)d.k;
+  const Products gemm{workspace, wk};
   FORGE_HIP(forge::moe_combine_bwd(ys, gates, pos_of, d_out, d.T, (int)d.h, k, d.bs, dgate, dys,
                                    s));
   // down projection: dgrad into the routed rows, wgrad per expert
@@ -678,8 +734,8 @@ forge_status moe_ffn_bwd(const forge_layer_cfg& c, const Dims& d, const forge_la
   // router: dl through the softmax (gates and aux loss), then its two products
   FORGE_HIP(forge::moe_router_bwd(probs, idx, dgate, counts, T, E, k, c.aux_coef, dl, s));
   uint16_t* db_r = d.fs ? at<uint16_t>(workspace, wk.db1) : db;
-  FORGE_HIP(forge::gemm(forge::kKC, forge::kMC, forge::kResidBF16,
-                        gargs(dl, d.E, w->w_router, d.h, db_r, d.h, d.T, d.h, d.E, dbs, d.h), s));
+  FORGE_HIP(gemm.here(forge::kKC, forge::kMC, forge::kResidBF16,
+                      gargs(dl, d.E, w->w_router, d.h, db_r, d.h, d.T, d.h, d.E, dbs, d.h), s));
   if (d.fs) {
     // shared expert: weight gradients beside the rest (side stream when there
     // is one), data gradient added to db
@@ -688,25 +744,24 @@ forge_status moe_ffn_bwd(const forge_layer_cfg& c, const Dims& d, const forge_la
     uint16_t* dA_s = at<uint16_t>(workspace, wk.dA_s);
     uint16_t* dgu_s = at<uint16_t>(workspace, wk.dgu_s);
     if (side) FORGE_HIP(link(s, ws, side->ev[5]));
-    FORGE_HIP(forge::gemm(forge::kMC, forge::kMC, wgrad_epi(g),
-                          scaled(gargs(d_out, d.h, act_s, d.fs, g->d_w_down_s, d.fs, d.h, d.fs,
-                                       d.T), d.bs), ws));
-    FORGE_HIP(forge::gemm(forge::kKC, forge::kMC, forge::kStoreBF16,
-                          scaled(gargs(d_out, d.h, w->w_down_s, d.fs, dA_s, d.fs, d.T, d.fs, d.h),
-                                 d.bs), s));
+    FORGE_HIP(gemm.wgrad(
+        wgrad_epi(g),
+        scaled(gargs(d_out, d.h, act_s, d.fs, g->d_w_down_s, d.fs, d.h, d.fs, d.T), d.bs), ws));
+    FORGE_HIP(gemm.here(forge::kKC, forge::kMC, forge::kStoreBF16,
+                        scaled(gargs(d_out, d.h, w->w_down_s, d.fs, dA_s, d.fs, d.T, d.fs, d.h),
+                               d.bs), s));
     FORGE_HIP(forge::swiglu_bwd(gu_s, dA_s, dgu_s, (int)d.T, (int)d.fs, s));
     if (side) FORGE_HIP(link(s, ws, side->ev[6]));
-    FORGE_HIP(forge::gemm(forge::kMC, forge::kMC, wgrad_epi(g),
-                          gargs(dgu_s, 2 * d.fs, bn, d.h, g->d_w_gate_up_s, d.h, 2 * d.fs, d.h,
-                                d.T), ws));
-    FORGE_HIP(forge::gemm(forge::kKC, forge::kMC, forge::kResidBF16,
-                          gargs(dgu_s, 2 * d.fs, w->w_gate_up_s, d.h, db, d.h, d.T, d.h, 2 * d.fs,
-                                db_r, d.h), s));
+    FORGE_HIP(gemm.wgrad(
+        wgrad_epi(g),
+        gargs(dgu_s, 2 * d.fs, bn, d.h, g->d_w_gate_up_s, d.h, 2 * d.fs, d.h, d.T), ws));
+    FORGE_HIP(gemm.here(forge::kKC, forge::kMC, forge::kResidBF16,
+                        gargs(dgu_s, 2 * d.fs, w->w_gate_up_s, d.h, db, d.h, d.T, d.h, 2 * d.fs,
+                              db_r, d.h), s));
   }
-  // router weight gradient: 64 x h output tiles over T tokens, split over T
-  FORGE_HIP(forge::gemm_wgrad_splitk(gargs(dl, d.E, bn, d.h, g->d_w_router, d.h, d.E, d.h, d.T),
-                                     forge::splitk_splits((int)d.E, (int)d.h, (int)d.T),
-                                     at<float>(workspace, wk.wpart), !g->overwrite, s));
+  // router weight gradient: E x h output tiles over T tokens
+  FORGE_HIP(gemm.here(forge::kMC, forge::kMC, wgrad_epi(g),
+                      gargs(dl, d.E, bn, d.h, g->d_w_router, d.h, d.E, d.h, d.T), s));
   return FORGE_OK;
 }
 
@@ -920,21 +975,22 @@ forge_status forge_layer_fwd(const forge_layer_cfg* cfg, const forge_layer_weigh
   uint16_t* o = cfg->recompute_attn ? at<uint16_t>(workspace, wk.o) : at<uint16_t>(saved, sv.o);
   float* lse = cfg->recompute_attn ? at<float>(workspace, wk.lse) : at<float>(saved, sv.lse);
 
+  const Products gemm{workspace, wk};
   uint16_t* qk_raw = d.qkn ? at<uint16_t>(saved, sv.qk_raw) : nullptr;
   float* rstd_qk = d.qkn ? at<float>(saved, sv.rstd_qk) : nullptr;
   if (forge_status e =
-          attn_block_fwd(*cfg, d, w, x_in, a, rstd1, qkv, o, lse, h1, qk_raw, rstd_qk, s))
+          attn_block_fwd(*cfg, d, w, x_in, a, rstd1, qkv, o, lse, h1, qk_raw, rstd_qk, gemm, s))
     return e;
   FORGE_HIP(forge::rmsnorm_fwd(h1, w->ffn_norm, bn, rstd2, (int)d.T, (int)d.h, cfg->rms_eps, s));
   if (moe) return moe_ffn_fwd(*cfg, d, w, saved, sv, workspace, wk, h1, x_out, aux_loss, s);
   uint16_t* gu = at<uint16_t>(saved, sv.gu);
   uint16_t* act = at<uint16_t>(saved, sv.act);
-  FORGE_HIP(forge::gemm(forge::kKC, forge::kKC, forge::kStoreBF16,
-                        gargs(bn, d.h, w->w_gate_up, d.h, gu, 2 * d.f, d.T, 2 * d.f, d.h), s));
+  FORGE_HIP(gemm.here(forge::kKC, forge::kKC, forge::kStoreBF16,
+                      gargs(bn, d.h, w->w_gate_up, d.h, gu, 2 * d.f, d.T, 2 * d.f, d.h), s));
   FORGE_HIP(forge::swiglu_fwd(gu, act, (int)d.T, (int)d.f, s));
-  FORGE_HIP(forge::gemm(forge::kKC, forge::kKC, forge::kResidBF16,
-                        scaled(gargs(act, d.f, w->w_down, d.f, x_out, d.h, d.T, d.h, d.f, h1, d.h),
-                               d.bs), s));
+  FORGE_HIP(gemm.here(forge::kKC, forge::kKC, forge::kResidBF16,
+                      scaled(gargs(act, d.f, w->w_down, d.f, x_out, d.h, d.T, d.h, d.f, h1, d.h),
+                             d.bs), s));
   return ok();
 }
 
@@ -975,6 +1031,7 @@ forge_status layer_bwd(const forge_layer_cfg* cfg, const forge_layer_weights* w,
   float* dgp = at<float>(workspace, wk.dg);
   const int nblk = forge::rmsnorm_bwd_blocks((int)d.T);
 
+  const Products gemm{workspace, wk};
   const uint16_t* o;
   const float* lse;
   if (cfg->recompute_attn) {
@@ -1029,9 +1086,9 @@ forge_status layer_bwd(const forge_layer_cfg* cfg, const forge_layer_weights* w,
     hipStream_t ws = side ? side->stream : s;
     if (opt) opt->lane = side;
     if (side) FORGE_HIP(link(s, ws, side->ev[0]));
-    FORGE_HIP(forge::gemm(forge::kMC, forge::kMC, wgrad_epi(g),
-                          scaled(gargs(d_out, d.h, act, d.f, g->d_w_down, d.f, d.h, d.f, d.T),
-                                 d.bs), ws));
+    FORGE_HIP(gemm.wgrad(
+        wgrad_epi(g), scaled(gargs(d_out, d.h, act, d.f, g->d_w_down, d.f, d.h, d.f, d.T), d.bs),
+        ws));
     // the weight-gradient product above is the side stream's only reader of
     // d_out; when d_in overlaps d_out, d_in is written only after it
     hipEvent_t d_out_read = nullptr;
@@ -1040,15 +1097,15 @@ forge_status layer_bwd(const forge_layer_cfg* cfg, const forge_layer_weights* w,
       d_out_read = side->ev[5];
       FORGE_HIP(hipEventRecord(d_out_read, ws));
     }
-    FORGE_HIP(forge::gemm(forge::kKC, forge::kMC, forge::kStoreBF16,
-                          scaled(gargs(d_out, d.h, w->w_down, d.f, dA, d.f, d.T, d.f, d.h), d.bs),
-                          s));
+    FORGE_HIP(gemm.here(forge::kKC, forge::kMC, forge::kStoreBF16,
+                        scaled(gargs(d_out, d.h, w->w_down, d.f, dA, d.f, d.T, d.f, d.h), d.bs),
+                        s));
     FORGE_HIP(forge::swiglu_bwd(gu, dA, dgu, (int)d.T, (int)d.f, s));
     if (side) FORGE_HIP(link(s, ws, side->ev[1]));
-    FORGE_HIP(forge::gemm(forge::kMC, forge::kMC, wgrad_epi(g),
-                          gargs(dgu, 2 * d.f, bn, d.h, g->d_w_gate_up, d.h, 2 * d.f, d.h, d.T), ws));
-    FORGE_HIP(forge::gemm(forge::kKC, forge::kMC, forge::kStoreBF16,
-                          gargs(dgu, 2 * d.f, w->w_gate_up, d.h, db, d.h, d.T, d.h, 2 * d.f), s));
+    FORGE_HIP(gemm.wgrad(
+        wgrad_epi(g), gargs(dgu, 2 * d.f, bn, d.h, g->d_w_gate_up, d.h, 2 * d.f, d.h, d.T), ws));
+    FORGE_HIP(gemm.here(forge::kKC, forge::kMC, forge::kStoreBF16,
+                        gargs(dgu, 2 * d.f, w->w_gate_up, d.h, db, d.h, d.T, d.h, 2 * d.f), s));
     // separate updates (dense weights): they start once the gate/up data
     // gradient is done, beside the attention backward; updating in the
     // weight-gradient epilogue instead would order each weight-gradient
@@ -1254,7 +1311,7 @@ forge_status forge_moe_route_noalloc(const float* logits, int32_t tokens, int32_
 // ---- output head ----------------------------------------------------------
 namespace {
 struct HeadWork {
-  size_t xn, rstd, z, row_loss, dxn, dg, total;
+  size_t xn, rstd, z, row_loss, dxn, dg, part, part_bytes, total;
 };
 forge_status check_head(const forge_head_cfg* c) {
   FORGE_CHECK(c != nullptr, FORGE_ERR_INVALID_ARG, "cfg is NULL");
@@ -1281,6 +1338,14 @@ HeadWork head_layout(const forge_head_cfg& c, long zrows) {
   w.row_loss = take(T * 4);
   w.dxn = take(T * h * 2);
   w.dg = take((size_t)forge::rmsnorm_bwd_blocks((int)T) * h * 4);
+  SplitScratch split, rows;
+  split.projection(split, T, V, h);
+  rows.projection(rows, zrows, V, h);
+  if (T % zrows) rows.projection(rows, T % zrows, V, h);  // the last chunk
+  // the streaming head takes no more than the plain one: it is there to save
+  // memory
+  w.part_bytes = std::min(split.bytes, rows.bytes);
+  w.part = take(w.part_bytes);
   w.total = off;
   return w;
 }
@@ -1335,18 +1400,19 @@ forge_status loss_impl(const forge_head_cfg* cfg, long chunk, const forge_bf16* 
   const int nblk = forge::rmsnorm_bwd_blocks((int)T);
 
   FORGE_HIP(forge::rmsnorm_fwd(x_L, final_norm, xn, rstd, (int)T, (int)h, cfg->rms_eps, s));
+  float* part = at<float>(workspace, hw.part);
   for (long t0 = 0; t0 < T; t0 += chunk) {
     const long n = std::min(chunk, T - t0);
     const uint16_t* xc = xn + t0 * h;
     FORGE_HIP(forge::gemm(forge::kKC, forge::kKC, forge::kStoreBF16,
-                          gargs(xc, h, w_lm, h, z, V, n, V, h), s));
+                          gargs(xc, h, w_lm, h, z, V, n, V, h), s, part, hw.part_bytes));
     FORGE_HIP(forge::ce_fwd_bwd(z, targets + t0, rl + t0, (int)n, (int)V,
                                 (float)(1.0 / (double)T),
                                 cfg->logit_scale == 0.0f ? 1.0f : cfg->logit_scale, s));
     FORGE_HIP(forge::gemm(forge::kKC, forge::kMC, forge::kStoreBF16,
-                          gargs(z, V, w_lm, h, dxn + t0 * h, h, n, h, V), s));
+                          gargs(z, V, w_lm, h, dxn + t0 * h, h, n, h, V), s, part, hw.part_bytes));
     FORGE_HIP(forge::gemm(forge::kMC, forge::kMC, forge::kAccF32,
-                          gargs(z, V, xc, h, d_w_lm, h, V, h, n), s));
+                          gargs(z, V, xc, h, d_w_lm, h, V, h, n), s, part, hw.part_bytes));
   }
   FORGE_HIP(forge::mean_reduce(rl, (int)T, (float)(1.0 / (double)T), loss_out, s));
   FORGE_HIP(forge::rmsnorm_bwd(x_L, final_norm, rstd, dxn, nullptr, d_x_L, dgp, (int)T, (int)h, s));

@@ -1027,27 +1027,27 @@ hipError_t launch_grouped_k(const GemmArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <bool ACC>
-__global__ __launch_bounds__(256) void splitk_reduce_k(const float* __restrict__ part, int S,
-                                                      long stride, int M, int N,
-                                                      float* __restrict__ out, long ldo) {
-  // out[m][n..n+3] (+)= sum over splits, in split order
+// C (op)= the sum of S fp32 partial products part[e][m][n] (leading dimension
+// ldp, `stride` apart) in split order, with the epilogue of the product they
+// are parts of; eight consecutive n per thread. HBM-bound: S partials read
+// once, C written once.
+template <int EPI>
+__global__ __launch_bounds__(256) void split_reduce_k(GemmArgs p, const float* __restrict__ part,
+                                                      int S, long stride, int ldp) {
+  const int nq = ldp / 8;
   const long q = (long)blockIdx.x * 256 + threadIdx.x;
-  const int nq = N / 4;
-  if (q >= (long)M * nq) return;
-  const int m = (int)(q / nq), n = (int)(q % nq) * 4;
-  const float* src = part + (long)m * N + n;
-  float4 acc = *reinterpret_cast<const float4*>(src);
+  if (q >= (long)p.M * nq) return;
+  const int m = (int)(q / nq), n = (int)(q % nq) * 8;
+  const float* src = part + (long)m * ldp + n;
+  f32x4_t a = *reinterpret_cast<const f32x4_t*>(src);
+  f32x4_t b = *reinterpret_cast<const f32x4_t*>(src + 4);
+#pragma unroll 4
   for (int e = 1; e < S; ++e) {
-    const float4 v = *reinterpret_cast<const float4*>(src + e * stride);
-    acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+    a += *reinterpret_cast<const f32x4_t*>(src + e * stride);
+    b += *reinterpret_cast<const f32x4_t*>(src + e * stride + 4);
   }
-  float4* o = reinterpret_cast<float4*>(out + (long)m * ldo + n);
-  if (ACC) {
-    const float4 c = *o;
-    acc.x += c.x; acc.y += c.y; acc.z += c.z; acc.w += c.w;
-  }
-  *o = acc;
+  float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+  store8_cached<EPI>(p, m, n, x);
 }
 
 constexpr int kCUs = 256;
@@ -1095,34 +1095,94 @@ double tile_cost(int layout, int t, long tiles, long K) {
          (double)K * (c.per_k + c.full_k * busy) * ((double)full + part);
 }
 
-Tile pick_tile(int layout, long M, long N, long K) {
-  int best = kT256;
-  double cost = tile_cost(layout, kT256, tile_count(kT256, M, N), K);
-  for (int t = kT256 + 1; t < kTiles; ++t) {
-    const double c = tile_cost(layout, t, tile_count(t, M, N), K);
-    if (c < cost) {
-      cost = c;
-      best = t;
+// A product may also split its reduction over S times as many workgroups
+// (caller's scratch: fp32 partials, then one pass that adds them in split
+// order), as long as the workgroups still fit one round: S partial tiles
+// cost their own traffic, so more rounds never paid. Measured, data gradient
+// (2048, 2048, 16384): 256 x 256 tiles 279 us on 64 CUs, 124 split four ways
+// (128 x 128 tiles unsplit: 200); weight gradient (4096, 1024, 16384): 308,
+// 129 (169).
+constexpr int kMaxSplit = 16;
+constexpr int kMinSplitK = 128;
+double reduce_cost(long S, long M, long N) { return 3.0 + (double)(S * M * N) * 8.0 / 5.5e6; }
+
+struct Plan {
+  Tile tile;
+  int splits;
+  long ks;  // reduction length of a split (the last one may be shorter)
+};
+
+long split_len(long K, int S) { return ((K + S - 1) / S + BK - 1) / BK * BK; }
+long partial_ld(long N) { return (N + 7) / 8 * 8; }
+size_t partial_bytes(int S, long M, long N) {
+  return S > 1 ? (size_t)S * (size_t)M * (size_t)partial_ld(N) * 4 : 0;
+}
+
+// scratch: bytes there are for partial tiles
+Plan pick_plan(int layout, long M, long N, long K, size_t scratch) {
+  Plan best = {kT256, 1, K};
+  // from a chip full of 256 x 256 tiles up no other tile is faster (8192 x
+  // 1536 x 1536 has 192: 36.9 us, 128 x 128 46.8, 128 x 256 50.1)
+  if (tile_count(kT256, M, N) >= kCUs) return best;
+  double cost = 1e30;
+  for (int t = 0; t < kTiles; ++t) {
+    const long tiles = tile_count(t, M, N);
+    for (int S = 1; S <= kMaxSplit; ++S) {
+      if (tiles * S > kCUs && S > 1) break;
+      if (K < (long)S * kMinSplitK && S > 1) break;
+      if (partial_bytes(S, M, N) > scratch) break;
+      const long ks = S > 1 ? split_len(K, S) : K;
+      if (S > 1 && (K + ks - 1) / ks != S) continue;  // the last split would be empty
+      const double c = tile_cost(layout, t, tiles * S, ks) + (S > 1 ? reduce_cost(S, M, N) : 0.0);
+      if (c < cost) {
+        cost = c;
+        best = {(Tile)t, S, ks};
+      }
     }
   }
-  return (Tile)best;
+  return best;
+}
+
+constexpr int layout_id(int la, int lb) { return la == kMC ? 2 : (lb == kMC ? 1 : 0); }
+
+template <int LA, int LB, int EPI, int GROUP>
+void launch_wave(const GemmArgs& a, long grid, hipStream_t s) {
+  hipLaunchKernelGGL((wave_kernel<64, 64, 4, 2, LA, LB, EPI, GROUP>), dim3((unsigned)grid),
+                     dim3(256), 0, s, a);
 }
 
 template <int LA, int LB, int EPI>
-hipError_t launch_wave(const GemmArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((wave_kernel<64, 64, 4, 2, LA, LB, EPI, 0>),
-                     dim3((unsigned)tile_count(kT64, a.M, a.N)), dim3(256), 0, s, a);
+hipError_t launch_split(const GemmArgs& a, const Plan& pl, float* part, hipStream_t s) {
+  GemmArgs p = a;
+  const long ldp = partial_ld(a.N), stride = (long)a.M * ldp;
+  p.C = part;
+  p.ldc = ldp;
+  p.alpha = 1.0f;
+  p.strideB = pl.ks;
+  p.strideC = stride;
+  const long grid = tile_count(pl.tile, a.M, a.N) * pl.splits;
+  switch (pl.tile) {
+    case kT64: launch_wave<LA, LB, kStoreF32, 3>(p, grid, s); break;
+    case kT128: launch_kernel<128, 128, 2, 2, LA, LB, kStoreF32, 3>(p, grid, s); break;
+    case kT128x256: launch_kernel<128, 256, 2, 4, LA, LB, kStoreF32, 3>(p, grid, s); break;
+    default: launch_kernel<256, 256, 2, 4, LA, LB, kStoreF32, 3>(p, grid, s); break;
+  }
+  const long items = (long)a.M * (ldp / 8);
+  hipLaunchKernelGGL(split_reduce_k<EPI>, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s,
+                     a, part, pl.splits, stride, (int)ldp);
   return hipGetLastError();
 }
 
 template <int LA, int LB, int EPI>
-hipError_t dispatch_tiles(const GemmArgs& a, hipStream_t s) {
+hipError_t dispatch_tiles(const GemmArgs& a, hipStream_t s, float* part, size_t part_bytes) {
   const long big = tile_count(kT256, a.M, a.N);
-  // from a chip full of 256 x 256 tiles up no other tile is faster (8192 x
-  // 1536 x 1536 has 192: 36.9 us, 128 x 128 46.8, 128 x 256 50.1)
-  const Tile t = big >= kCUs ? kT256
-                             : pick_tile(LA == kMC ? 2 : (LB == kMC ? 1 : 0), a.M, a.N, a.K);
-  if (t == kT64) return launch_wave<LA, LB, EPI>(a, s);
+  const Plan pl = pick_plan(layout_id(LA, LB), a.M, a.N, a.K, part ? part_bytes : 0);
+  if (pl.splits > 1) return launch_split<LA, LB, EPI>(a, pl, part, s);
+  const Tile t = pl.tile;
+  if (t == kT64) {
+    launch_wave<LA, LB, EPI, 0>(a, tile_count(kT64, a.M, a.N), s);
+    return hipGetLastError();
+  }
   if (t == kT128) return launch<128, 128, 2, 2, LA, LB, EPI>(a, s);
   if (t == kT128x256) return launch<128, 256, 2, 4, LA, LB, EPI>(a, s);
   if constexpr (LA == kKC && LB == kKC) {
@@ -1177,60 +1237,32 @@ hipError_t gemm_grouped_k(GemmEpilogue epi, const GemmArgs& a, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
-int splitk_splits(int M, int N, int K) {
-  const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
-  if (tiles >= 128 || K < 1024) return 1;
-  int S = (int)((256 + tiles - 1) / tiles);
-  S = S > K / 512 ? K / 512 : S;
-  return S < 1 ? 1 : (S > 32 ? 32 : S);
+size_t gemm_split_bytes(GemmLayout la, GemmLayout lb, long M, long N, long K) {
+  if (M <= 0 || N <= 0) return 0;
+  return partial_bytes(pick_plan(layout_id(la, lb), M, N, K, SIZE_MAX).splits, M, N);
 }
 
-hipError_t gemm_wgrad_splitk(const GemmArgs& a, int splits, float* partial, bool accumulate,
-                             hipStream_t s) {
-  if (a.M <= 0 || a.N <= 0) return hipSuccess;
-  if (splits <= 1 || a.K <= 0) return gemm(kMC, kMC, accumulate ? kAccF32 : kStoreF32, a, s);
-  const long ks = ((a.K + splits - 1) / splits + BK - 1) / BK * BK;
-  const int S = (int)((a.K + ks - 1) / ks);
-  GemmArgs p = a;
-  p.C = partial;
-  p.ldc = a.N;
-  p.strideB = ks;
-  p.strideC = (long)a.M * a.N;
-  p.groups = S;
-  const long tiles = (long)S * ((a.M + 127) / 128) * ((a.N + 127) / 128);
-  launch_kernel<128, 128, 2, 2, kMC, kMC, kStoreF32, 3>(p, tiles, s);
-  const long n4 = (long)a.M * (a.N / 4);
-  const dim3 grid((unsigned)((n4 + 255) / 256));
-  if (accumulate)
-    hipLaunchKernelGGL(splitk_reduce_k<true>, grid, dim3(256), 0, s, partial, S, (long)a.M * a.N,
-                       a.M, a.N, reinterpret_cast<float*>(a.C), a.ldc);
-  else
-    hipLaunchKernelGGL(splitk_reduce_k<false>, grid, dim3(256), 0, s, partial, S, (long)a.M * a.N,
-                       a.M, a.N, reinterpret_cast<float*>(a.C), a.ldc);
-  return hipGetLastError();
-}
-
-hipError_t gemm(GemmLayout la, GemmLayout lb, GemmEpilogue epi, const GemmArgs& a,
-                hipStream_t s) {
+hipError_t gemm(GemmLayout la, GemmLayout lb, GemmEpilogue epi, const GemmArgs& a, hipStream_t s,
+                float* part, size_t part_bytes) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   if (la == kKC && lb == kKC) {
     switch (epi) {
-      case kStoreBF16: return dispatch_tiles<kKC, kKC, kStoreBF16>(a, s);
-      case kResidBF16: return dispatch_tiles<kKC, kKC, kResidBF16>(a, s);
-      case kAccF32: return dispatch_tiles<kKC, kKC, kAccF32>(a, s);
-      case kStoreF32: return dispatch_tiles<kKC, kKC, kStoreF32>(a, s);
+      case kStoreBF16: return dispatch_tiles<kKC, kKC, kStoreBF16>(a, s, part, part_bytes);
+      case kResidBF16: return dispatch_tiles<kKC, kKC, kResidBF16>(a, s, part, part_bytes);
+      case kAccF32: return dispatch_tiles<kKC, kKC, kAccF32>(a, s, part, part_bytes);
+      case kStoreF32: return dispatch_tiles<kKC, kKC, kStoreF32>(a, s, part, part_bytes);
       default: break;
     }
   } else if (la == kKC && lb == kMC) {
     switch (epi) {
-      case kStoreBF16: return dispatch_tiles<kKC, kMC, kStoreBF16>(a, s);
-      case kResidBF16: return dispatch_tiles<kKC, kMC, kResidBF16>(a, s);
+      case kStoreBF16: return dispatch_tiles<kKC, kMC, kStoreBF16>(a, s, part, part_bytes);
+      case kResidBF16: return dispatch_tiles<kKC, kMC, kResidBF16>(a, s, part, part_bytes);
       default: break;
     }
   } else if (la == kMC && lb == kMC) {
     switch (epi) {
-      case kAccF32: return dispatch_tiles<kMC, kMC, kAccF32>(a, s);
-      case kStoreF32: return dispatch_tiles<kMC, kMC, kStoreF32>(a, s);
+      case kAccF32: return dispatch_tiles<kMC, kMC, kAccF32>(a, s, part, part_bytes);
+      case kStoreF32: return dispatch_tiles<kMC, kMC, kStoreF32>(a, s, part, part_bytes);
       default: break;
     }
   }

@@ -57,23 +57,19 @@ struct GemmArgs {
 // Host-side shape rules (checked by the caller): K-contiguous operands need
 // K % 8 == 0; M/N-contiguous operands need that dimension % 8 == 0; leading
 // dimensions % 8 == 0; base pointers 16-byte aligned.
+// part (16-byte aligned, part_bytes): scratch that lets a product of few output
+// tiles and a long reduction split the reduction over more workgroups, fp32
+// partials added in a fixed order; gemm_split_bytes is what the product would
+// use (0: it does not split). With less scratch it splits into fewer parts.
+size_t gemm_split_bytes(GemmLayout la, GemmLayout lb, long M, long N, long K);
 hipError_t gemm(GemmLayout la, GemmLayout lb, GemmEpilogue epi, const GemmArgs& a,
-                hipStream_t stream);
+                hipStream_t stream, float* part = nullptr, size_t part_bytes = 0);
 // Grouped forms, one product per group e with rows [g_off[e], g_off[e+1]):
 //   M-grouped (KC or MC B): C rows g_off[e].. = A rows g_off[e].. x B_e, where
 //     B_e = B + e * strideB; M is an upper bound of the total rows (T * k).
 //   K-grouped (MC, MC): C_e (+)= sum over rows g_off[e].. of A^T B, C_e = C + e * strideC.
 hipError_t gemm_grouped_m(GemmLayout lb, GemmEpilogue epi, const GemmArgs& a, hipStream_t s);
 hipError_t gemm_grouped_k(GemmEpilogue epi, const GemmArgs& a, hipStream_t s);
-// Weight gradient C += A^T B (or C = A^T B when !accumulate), both operands
-// M/N-contiguous, with the reduction split
-// into `splits` uniform slices: fp32 partials [splits][M][N] in `partial`,
-// then summed in slice order into C. For products with few output tiles and
-// a long reduction (N % 4 == 0). splitk_splits picks the split count (1 =
-// plain GEMM, no partials needed).
-int splitk_splits(int M, int N, int K);
-hipError_t gemm_wgrad_splitk(const GemmArgs& a, int splits, float* partial, bool accumulate,
-                             hipStream_t s);
 
 // --------------------------------------------------------- elementwise ----
 hipError_t rmsnorm_fwd(const uint16_t* x, const uint16_t* g, uint16_t* y, float* rstd,

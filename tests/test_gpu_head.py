@@ -38,7 +38,9 @@ def run_head(T, h, V, seed, chunk=0):
                 dg=(host_f64(dg) - 0.25, r_dg), dw=(host_f64(dw) + 0.125, r_dw))
 
 
-@pytest.mark.parametrize("T,h,V", [(128, 256, 1024), (200, 64, 1032), (64, 2048, 32000)])
+# (264, 264, 8200): the input gradient splits its reduction over V
+@pytest.mark.parametrize("T,h,V", [(128, 256, 1024), (200, 64, 1032), (64, 2048, 32000),
+                                   (264, 264, 8200)])
 def test_head_parity(T, h, V):
     banner(f"head T={T} h={h} V={V}")
     r = run_head(T, h, V, seed=T + V)

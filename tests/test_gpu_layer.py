@@ -163,3 +163,30 @@ def test_overwrite_grads_equal_accumulate_into_zeros(which):
     torch.cuda.synchronize()
     for k, v in layer.g.items():
         assert torch.equal(v, acc[k]), k
+
+
+@pytest.mark.parametrize("over", [
+    # few tokens, wide heads and FFN: the O and down forward products and the
+    # QKV and gate/up data gradients split (K 4096 to 8208)
+    dict(batch=1, seq=72, hidden=512, n_heads=32, n_kv_heads=8, head_dim=128, ffn=4104),
+    # many tokens, narrow layer: all four weight gradients split (K = 2064)
+    dict(batch=2, seq=1032, hidden=264, n_heads=4, n_kv_heads=1, head_dim=64, ffn=520),
+])
+def test_layer_split_reductions(over):
+    """Layers whose products split their reduction over workgroups, against
+    the oracle; and a forward without a workspace, whose products do not
+    split: the same up to the order of the fp32 sums (one bf16 rounding of
+    the output either way)."""
+    import torch
+    from paper_2609_13645_amd import _lib, runtime
+    cfg = fi.config("tiny", **over)
+    banner(f"layer split reductions {over}")
+    check(*run_layer(cfg, seed=71))
+    inp = fi.layer_inputs(cfg, 71)
+    layer = runtime.Layer(cfg, inp["weights"])
+    x = runtime.to_device_bf16(inp["x"])
+    a, b = torch.empty_like(x), torch.empty_like(x)
+    layer.fwd(x, a)
+    _lib.forge_layer_fwd(layer.c, layer.weights, x, b, layer.saved, None)
+    torch.cuda.synchronize()
+    assert rel_fro(host_f64(a), host_f64(b)) <= 4e-3
