@@ -1010,13 +1010,17 @@ hipError_t launch(const GemmArgs& a, hipStream_t s) {
 }
 
 // M-grouped: at most M / BM + groups m-tiles exist, whatever the group sizes.
+// Real tiles <= (M / BM + groups) * tiles_n; rounded up so that every XCD's
+// share of the workgroups covers ceil(real / 8) tiles.
+template <int BM, int BN>
+long grouped_m_grid(const GemmArgs& a) {
+  const long mt = a.M / BM + a.groups;
+  return ((mt * ((a.N + BN - 1) / BN) + NUM_XCD - 1) / NUM_XCD + 1) * NUM_XCD;
+}
+
 template <int BM, int BN, int WAVES_M, int WAVES_N, int LB, int EPI>
 hipError_t launch_grouped_m(const GemmArgs& a, hipStream_t s) {
-  // real tiles <= (M / BM + groups) * tiles_n; rounded up so that every XCD's
-  // share of the workgroups covers ceil(real / 8) tiles
-  const long mt = a.M / BM + a.groups;
-  const long tiles = ((mt * ((a.N + BN - 1) / BN) + NUM_XCD - 1) / NUM_XCD + 1) * NUM_XCD;
-  launch_kernel<BM, BN, WAVES_M, WAVES_N, kKC, LB, EPI, 1>(a, tiles, s);
+  launch_kernel<BM, BN, WAVES_M, WAVES_N, kKC, LB, EPI, 1>(a, grouped_m_grid<BM, BN>(a), s);
   return hipGetLastError();
 }
 
@@ -1221,19 +1225,68 @@ hipError_t dispatch_tiles(const GemmArgs& a, hipStream_t s, float* part, size_t 
 
 }  // namespace
 
+namespace {
+// Tile of a product over row groups, from the same estimates. The host knows
+// the rows' upper bound, not the groups' sizes: a group of r rows is taken to
+// have r / BM + 1/2 m-tiles, at least one. The smaller tile has to win by 5 %
+// (groups of about 400 rows estimate alike and run better on 256 rows), and
+// 64 x 64 tiles are for launches of at most two rounds (beyond, every tile
+// streams its own weights). Measured, rows per group x groups, forward
+// gate/up: 100 x 160 (N 1024, K 2048) 186 us on 256 x 256, 170 on 128 x 256,
+// 234 on 64 x 64; 75 x 8 (2048, 1024) 30, 19, 13.5; 1024 x 64 (2816, 2048)
+// 1000, 1027, 1575.
+Tile pick_grouped_tile(int layout, long rows, long groups, long N, long K) {
+  Tile best = kT256;
+  double cost = 1e30;
+  for (const Tile t : {kT256, kT128x256, kT64}) {
+    const double per = (double)rows / (double)groups / kTileM[t] + 0.5;
+    const long tiles = (long)((per < 1.0 ? 1.0 : per) * (double)groups) *
+                       ((N + kTileN[t] - 1) / kTileN[t]);
+    if (t == kT64 && tiles > 2 * kSlots[kT64]) continue;
+    const double c = tile_cost(layout, t, tiles, K);
+    if (c < 0.95 * cost) {
+      cost = c;
+      best = t;
+    }
+  }
+  return best;
+}
+
+template <int LB>
+hipError_t launch_grouped_rows(const GemmArgs& a, hipStream_t s) {
+  switch (pick_grouped_tile(layout_id(kKC, LB), a.M, a.groups, a.N, a.K)) {
+    case kT64:
+      launch_wave<kKC, LB, kStoreBF16, 1>(a, grouped_m_grid<64, 64>(a), s);
+      return hipGetLastError();
+    case kT128x256: return launch_grouped_m<128, 256, 2, 4, LB, kStoreBF16>(a, s);
+    default: break;
+  }
+  // the transposing reads of an M/N-contiguous weight on the narrow side of
+  // the wave tile (128 x 64 waves), as in the ungrouped data gradient
+  return LB == kKC ? launch_grouped_m<256, 256, 4, 2, LB, kStoreBF16>(a, s)
+                   : launch_grouped_m<256, 256, 2, 4, LB, kStoreBF16>(a, s);
+}
+
+}  // namespace
+
 hipError_t gemm_grouped_m(GemmLayout lb, GemmEpilogue epi, const GemmArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0 || a.groups <= 0) return hipSuccess;
-  if (lb == kKC && epi == kStoreBF16) return launch_grouped_m<256, 256, 4, 2, kKC, kStoreBF16>(a, s);
-  if (lb == kMC && epi == kStoreBF16) return launch_grouped_m<256, 256, 2, 4, kMC, kStoreBF16>(a, s);
+  if (lb == kKC && epi == kStoreBF16) return launch_grouped_rows<kKC>(a, s);
+  if (lb == kMC && epi == kStoreBF16) return launch_grouped_rows<kMC>(a, s);
   return hipErrorInvalidValue;
 }
 
+// 128 x 64 waves: as fast as 64 x 128 with the AdamW epilogue (its streams bound
+// it) and 2-10 % faster without (64 groups of 1024 rows, 2816 x 2048: 1004 us
+// against 1018; 160 of 100, 1024 x 2048: 332 against 370). For groups of about
+// 100 rows 128 x 128 tiles are 12 % faster alone (294 us), but their many small
+// workgroups hold up the kernels beside them: layer 2034 -> 2118 us.
 hipError_t gemm_grouped_k(GemmEpilogue epi, const GemmArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0 || a.groups <= 0) return hipSuccess;
-  if (epi == kAccF32) return launch_grouped_k<256, 256, 4, 2, kAccF32>(a, s);
-  if (epi == kStoreF32) return launch_grouped_k<256, 256, 4, 2, kStoreF32>(a, s);
-  if (epi == kAccF32Adam) return launch_grouped_k<256, 256, 4, 2, kAccF32Adam>(a, s);
-  if (epi == kStoreF32Adam) return launch_grouped_k<256, 256, 4, 2, kStoreF32Adam>(a, s);
+  if (epi == kAccF32) return launch_grouped_k<256, 256, 2, 4, kAccF32>(a, s);
+  if (epi == kStoreF32) return launch_grouped_k<256, 256, 2, 4, kStoreF32>(a, s);
+  if (epi == kAccF32Adam) return launch_grouped_k<256, 256, 2, 4, kAccF32Adam>(a, s);
+  if (epi == kStoreF32Adam) return launch_grouped_k<256, 256, 2, 4, kStoreF32Adam>(a, s);
   return hipErrorInvalidValue;
 }
 

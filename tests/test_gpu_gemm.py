@@ -214,7 +214,8 @@ GROUP_SIZES = [0, 37, 256, 1, 300, 0, 129, 8, 513]
 
 
 @pytest.mark.parametrize("lb", [KC, MC])
-@pytest.mark.parametrize("N,K", [(136, 64), (264, 200)])
+# few tiles (64 x 64 at the first two sizes), 128 x 256 tiles
+@pytest.mark.parametrize("N,K", [(136, 64), (264, 200), (3080, 1000)])
 def test_grouped_rows_integer_exact(lb, N, K):
     """Per-group products over expert-major rows, ragged and empty groups;
     rows past the last offset are never written."""
