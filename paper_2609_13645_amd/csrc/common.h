@@ -54,7 +54,6 @@ __device__ __forceinline__ uint4 pack8(const float* f) {
                     pack2(f[4], f[5]), pack2(f[6], f[7]));
 }
 
-// Wave-wide (64 lanes) butterfly reductions.
 // One AdamW element (App. F, fused clip + Adam + cast), shared by the
 // standalone update and the GEMM's fused weight-gradient epilogue so that
 // both give the same bits:
@@ -73,14 +72,34 @@ __device__ __forceinline__ void adam1(float& p, float& m, float& v, float g, flo
   p = __builtin_fmaf(-lr, upd, p);
 }
 
+// Wave-wide (64 lanes) butterfly reductions, the result in every lane.
+// Lanes l ^ 32 and l ^ 16 come through LDS shuffles; inside a row of 16 lanes
+// a DPP move on the VALU replaces each shuffle: a rotation by 8 is l ^ 8, and
+// once lanes l and l ^ 8 agree a rotation by 4 reads the value of l ^ 4. The
+// pairs added are those of the shuffle butterfly, so the sum has its bits.
+template <int CTRL>
+__device__ __forceinline__ float dpp_mov(float v) {
+  const int x = __builtin_bit_cast(int, v);
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(x, x, CTRL, 0xF, 0xF, false));
+}
+constexpr int kRowRor8 = 0x128, kRowRor4 = 0x124, kQuadSwap2 = 0x4E, kQuadSwap1 = 0xB1;
+
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+  v += __shfl_xor(v, 32, kWave);
+  v += __shfl_xor(v, 16, kWave);
+  v += dpp_mov<kRowRor8>(v);
+  v += dpp_mov<kRowRor4>(v);
+  v += dpp_mov<kQuadSwap2>(v);
+  v += dpp_mov<kQuadSwap1>(v);
   return v;
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
+  v = fmaxf(v, __shfl_xor(v, 32, kWave));
+  v = fmaxf(v, __shfl_xor(v, 16, kWave));
+  v = fmaxf(v, dpp_mov<kRowRor8>(v));
+  v = fmaxf(v, dpp_mov<kRowRor4>(v));
+  v = fmaxf(v, dpp_mov<kQuadSwap2>(v));
+  v = fmaxf(v, dpp_mov<kQuadSwap1>(v));
   return v;
 }
 

@@ -234,7 +234,7 @@ Work work_layout(const forge_layer_cfg& c) {
     w.dgu = take(d.R * 2 * d.fe * 2);
     w.logits = take(d.T * d.E * 4);
     w.blk = take((size_t)forge::moe_sort_blocks((int)d.T) * d.E * 4);
-    w.colsum = take((1 + (size_t)forge::moe_aux_blocks((int)d.T)) * d.E * 4);
+    w.colsum = take((size_t)forge::moe_sort_blocks((int)d.T) * d.E * 4);
     w.dys = take(d.R * d.h * 2);
     w.dxs = take(d.R * d.h * 2);
     w.dgate = take(d.R * 4);
@@ -644,7 +644,7 @@ forge_status moe_ffn_fwd(const forge_layer_cfg& c, const Dims& d, const forge_la
                       gargs(bn, d.h, w->w_router, d.h, logits, d.E, d.T, d.E, d.h), s));
   FORGE_HIP(forge::moe_route(logits, T, E, k, idx, gates, probs, s));
   FORGE_HIP(forge::moe_sort(idx, T, E, k, at<int32_t>(workspace, wk.blk), counts, offsets, perm,
-                            pos_of, s));
+                            pos_of, s, probs, c.aux_coef, at<float>(workspace, wk.colsum), aux));
   FORGE_HIP(forge::moe_gather(bn, perm, d.R, (int)d.h, k, xs, s));
   FORGE_HIP(forge::gemm_grouped_m(
       forge::kKC, forge::kStoreBF16,
@@ -672,8 +672,6 @@ forge_status moe_ffn_fwd(const forge_layer_cfg& c, const Dims& d, const forge_la
     resid = h1s;
   }
   FORGE_HIP(forge::moe_combine(ys, gates, pos_of, resid, d.T, (int)d.h, k, d.bs, out, s));
-  FORGE_HIP(forge::moe_aux_loss(probs, counts, T, E, k, c.aux_coef,
-                                at<float>(workspace, wk.colsum), aux, s));
   return FORGE_OK;
 }
 
@@ -1290,10 +1288,10 @@ forge_status forge_moe_route_noalloc(const float* logits, int32_t tokens, int32_
   FORGE_CHECK((size_t)tokens * top_k <= kRouteScratchEntries, FORGE_ERR_UNSUPPORTED,
               "tokens * top_k = %lld exceeds the fixed scratch limit %zu",
               (long long)tokens * top_k, kRouteScratchEntries);
-  FORGE_CHECK((size_t)forge::moe_sort_blocks(tokens) * n_experts <= kRouteScratchHist,
+  FORGE_CHECK(((size_t)tokens + 127) / 128 * n_experts <= kRouteScratchHist,
               FORGE_ERR_UNSUPPORTED,
               "ceil(tokens / 128) * n_experts = %lld exceeds the fixed scratch limit %zu",
-              (long long)forge::moe_sort_blocks(tokens) * n_experts, kRouteScratchHist);
+              ((long long)tokens + 127) / 128 * n_experts, kRouteScratchHist);
   for (const void* p : {(const void*)logits, (const void*)idx, (const void*)gates,
                         (const void*)probs, (const void*)counts, (const void*)offsets,
                         (const void*)perm})

@@ -154,10 +154,13 @@ hipError_t moe_route(const float* logits, int T, int E, int k, int32_t* idx, flo
                      float* probs, hipStream_t s);
 // Blocks of the counting sort; block_counts needs moe_sort_blocks(T) * E ints.
 int moe_sort_blocks(int T);
-// counts [E], offsets [E + 1], perm / pos_of [T k] (canonical order).
+// counts [E], offsets [E + 1], perm / pos_of [T k] (canonical order). With aux,
+// the layer's load-balance loss over probs [T, E] is added to it (colsum:
+// moe_sort_blocks(T) * E floats of scratch).
 hipError_t moe_sort(const int32_t* idx, int T, int E, int k, int32_t* block_counts,
                     int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* pos_of,
-                    hipStream_t s);
+                    hipStream_t s, const float* probs = nullptr, float alpha = 0.0f,
+                    float* colsum = nullptr, float* aux = nullptr);
 hipError_t moe_gather(const uint16_t* b, const int32_t* perm, long rows, int h, int k,
                       uint16_t* xs, hipStream_t s);
 // out = h1 + scale * sum_j gate_j ys_j; backward with the same scale.
@@ -169,10 +172,6 @@ hipError_t moe_combine_bwd(const uint16_t* ys, const float* gates, const int32_t
                            uint16_t* dys, hipStream_t s);
 hipError_t moe_scatter_back(const uint16_t* dxs, const int32_t* pos_of, long T, int h, int k,
                             uint16_t* db, hipStream_t s);
-// colsum: E column sums followed by moe_aux_blocks(T) * E block partials.
-int moe_aux_blocks(int T);
-hipError_t moe_aux_loss(const float* probs, const int32_t* counts, int T, int E, int k,
-                        float alpha, float* colsum, float* aux, hipStream_t s);
 hipError_t moe_router_bwd(const float* probs, const int32_t* idx, const float* dgate,
                           const int32_t* counts, int T, int E, int k, float alpha, uint16_t* dl,
                           hipStream_t s);

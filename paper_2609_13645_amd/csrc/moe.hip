@@ -8,54 +8,61 @@
 //    order, -0 equal to +0, NaN below -inf; ties to the lower expert id), so
 //    every index lies in [0, E) whatever the logits hold. Gates are the
 //    softmax probabilities of the chosen experts (no renormalisation).
-//  * permutation: a counting sort that is deterministic by construction —
-//    per-block expert histograms, a fixed-order scan over blocks, then each
-//    block assigns ranks in flat (token, slot) order with wave ballots, so
-//    the order is expert-major, token ascending, slot ascending.
+//  * permutation: a counting sort that is deterministic by construction:
+//    per-block expert histograms, then each block adds up the histograms
+//    itself (the whole scan, in one launch) and assigns ranks in flat
+//    (token, slot) order with wave ballots, so the order is expert-major,
+//    token ascending, slot ascending.
 //  * gather / combine / their backward move whole bf16 rows with 16-byte
 //    vectors; every sum over the k slots of a token runs in slot order.
 //  * the load-balance auxiliary loss alpha * E * sum_e f_e P_e and its
 //    gradient through the softmax (f_e = count_e / (T k) is a constant);
-//    the column sums behind P_e are per-block partials summed in block order.
-#include <climits>
-
+//    the column sums behind P_e are per-block partials of the sort's blocks,
+//    added in a fixed order by its second launch.
 #include "common.h"
 #include "kernels.h"
 
 namespace forge {
 namespace {
 
-constexpr int kSortTokens = 128;  // tokens per counting-sort block
+constexpr int kSortTokens = 128;  // tokens per counting-sort block, at least
+constexpr int kSortBlocks = 512;  // counting-sort blocks, at most
 constexpr int kMaxE = 256;        // experts (four per lane of a wave)
-constexpr int kSlots = kMaxE / 64;
 
 // ------------------------------------------------------------- routing ----
 // Order key of a logit for the top-k choice: larger key = preferred. The
 // integer image of the float is monotone in its value; -0 is first made +0
-// (they compare equal) and NaN gets the lowest key of all.
+// (they compare equal), NaN gets the lowest key of all, 1, and 0 stands for an
+// expert that is taken or absent (-inf, the lowest number, has 0x007FFFFF).
 __device__ __forceinline__ uint32_t order_key(float f) {
   if (f == 0.0f) f = 0.0f;
   const int b = __float_as_int(f);
-  const int key = b >= 0 ? b : (b ^ 0x7FFFFFFF);
-  return (uint32_t)(f != f ? INT_MIN : key) ^ 0x80000000u;
+  const uint32_t key = (uint32_t)(b >= 0 ? b : (b ^ 0x7FFFFFFF)) ^ 0x80000000u;
+  return f != f ? 1u : key;
 }
-// Candidate word: order key, then the expert id reversed (a lower id wins a
-// tie of keys), then a 1 so that every real candidate is above 0, which
-// marks an expert that is taken or absent.
-__device__ __forceinline__ uint64_t cand_word(float l, int e) {
-  return ((uint64_t)order_key(l) << 32) | ((uint64_t)(kMaxE - 1 - e) << 1) | 1ull;
+// Largest value of the wave, uniform: a DPP reduction into lane 63 (row
+// shifts, then the rows' last lanes broadcast; lanes without a source take
+// the identity 0).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t max_dpp(uint32_t v) {
+  const uint32_t w = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+  return w > v ? w : v;
 }
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const uint32_t lo = __shfl_xor((uint32_t)v, o, 64);
-    const uint32_t hi = __shfl_xor((uint32_t)(v >> 32), o, 64);
-    const uint64_t w = ((uint64_t)hi << 32) | lo;
-    v = w > v ? w : v;
-  }
-  return v;
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  v = max_dpp<0x111, 0xF>(v);  // row_shr 1, 2, 4, 8
+  v = max_dpp<0x112, 0xF>(v);
+  v = max_dpp<0x114, 0xF>(v);
+  v = max_dpp<0x118, 0xF>(v);
+  v = max_dpp<0x142, 0xA>(v);  // row_bcast 15 into rows 1 and 3
+  v = max_dpp<0x143, 0xC>(v);  // row_bcast 31 into rows 2 and 3
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+// NS: expert slots per lane (E <= 64 NS). Latency-bound, one wave per token:
+// each of the k rounds is one DPP maximum of 32-bit keys and a ballot that
+// finds its lowest expert (64-bit keys through LDS shuffles before: 8192
+// tokens, 64 experts, top 8 in 15 us).
+template <int NS>
 __global__ __launch_bounds__(256) void route_k(const float* __restrict__ logits, int T, int E,
                                                int k, int32_t* __restrict__ idx,
                                                float* __restrict__ gates,
@@ -63,10 +70,10 @@ __global__ __launch_bounds__(256) void route_k(const float* __restrict__ logits,
   const int lane = threadIdx.x & 63;
   const long t = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= T) return;
-  float l[kSlots], p[kSlots];
+  float l[NS], p[NS];
   float mx = -INFINITY;
 #pragma unroll
-  for (int i = 0; i < kSlots; ++i) {
+  for (int i = 0; i < NS; ++i) {
     const int e = lane + 64 * i;
     l[i] = e < E ? logits[t * E + e] : -INFINITY;
     mx = fmaxf(mx, l[i]);
@@ -74,111 +81,197 @@ __global__ __launch_bounds__(256) void route_k(const float* __restrict__ logits,
   mx = wave_max(mx);
   float sum = 0.0f;
 #pragma unroll
-  for (int i = 0; i < kSlots; ++i) {
+  for (int i = 0; i < NS; ++i) {
     const int e = lane + 64 * i;
     p[i] = e < E ? __expf(l[i] - mx) : 0.0f;
     sum += p[i];
   }
   sum = wave_sum(sum);
-  uint64_t cand[kSlots];
+  uint32_t key[NS];
 #pragma unroll
-  for (int i = 0; i < kSlots; ++i) {
+  for (int i = 0; i < NS; ++i) {
     const int e = lane + 64 * i;
     p[i] /= sum;
     if (e < E) probs[t * E + e] = p[i];
-    cand[i] = e < E ? cand_word(l[i], e) : 0ull;
+    key[i] = e < E ? order_key(l[i]) : 0u;
   }
+  // lane j % 64 keeps choice j; every 64 choices (and the last ones) are
+  // stored together
+  int my_e = 0;
+  float my_g = 0.0f;
   for (int j = 0; j < k; ++j) {
-    uint64_t best = cand[0];
+    uint32_t best = key[0];
 #pragma unroll
-    for (int i = 1; i < kSlots; ++i) best = cand[i] > best ? cand[i] : best;
-    best = wave_max_u64(best);
-    // k <= E, so a real candidate is left in every round
-    const int e = kMaxE - 1 - (int)((best >> 1) & (kMaxE - 1));
-    const int owner = e & 63, slot = e >> 6;
-    float ps = p[0];
+    for (int i = 1; i < NS; ++i) best = key[i] > best ? key[i] : best;
+    best = wave_max_u32(best);
+    // k <= E, so a real candidate is left in every round; the lowest slot
+    // (then lane) that holds the key is the lowest expert id
+    int e = 0;
+    float g = 0.0f;
+    bool found = false;
 #pragma unroll
-    for (int i = 1; i < kSlots; ++i) ps = slot == i ? p[i] : ps;
-    const float g = __shfl(ps, owner, 64);
-    if (lane == 0) {
-      idx[t * k + j] = e;
-      gates[t * k + j] = g;
+    for (int i = 0; i < NS; ++i) {
+      const uint64_t hit = __ballot(key[i] == best);
+      if (!found && hit) {
+        found = true;
+        const int o = __ffsll((unsigned long long)hit) - 1;
+        e = o + 64 * i;
+        g = __builtin_bit_cast(
+            float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, p[i]), o));
+        if (lane == o) key[i] = 0u;
+      }
     }
-#pragma unroll
-    for (int i = 0; i < kSlots; ++i)
-      if (lane == owner && slot == i) cand[i] = 0ull;
+    if (lane == (j & 63)) {
+      my_e = e;
+      my_g = g;
+    }
+    if ((j & 63) == 63 || j == k - 1) {
+      const int j0 = j & ~63;
+      if (lane <= (j & 63)) {
+        idx[t * k + j0 + lane] = my_e;
+        gates[t * k + j0 + lane] = my_g;
+      }
+    }
   }
 }
 
-// Per-block expert histogram of the flat (token, slot) entries (entries
-// outside [0, E) are not counted).
+// Per-block expert histogram of the flat (token, slot) entries of `tok`
+// tokens (entries outside [0, E) are not counted) and, with probs, the block's
+// column sums of the router probabilities, colsum[block][e]: 256 / E groups of
+// threads sum interleaved tokens, the groups in order.
 __global__ __launch_bounds__(256) void sort_count_k(const int32_t* __restrict__ idx, int T, int E,
-                                                    int k, int32_t* __restrict__ block_counts) {
+                                                    int k, int tok,
+                                                    int32_t* __restrict__ block_counts,
+                                                    const float* __restrict__ probs,
+                                                    float* __restrict__ colsum) {
   __shared__ int hist[kMaxE];
+  __shared__ float part[256];
   hist[threadIdx.x] = 0;
   __syncthreads();
-  const long f0 = (long)blockIdx.x * kSortTokens * k;
-  const long f1 = min((long)T * k, f0 + (long)kSortTokens * k);
-  for (long f = f0 + threadIdx.x; f < f1; f += blockDim.x) {
+  const long t0 = (long)blockIdx.x * tok;
+  const long t1 = min((long)T, t0 + tok);
+  for (long f = t0 * k + threadIdx.x; f < t1 * k; f += blockDim.x) {
     const int e = idx[f];
     if ((unsigned)e < (unsigned)E) atomicAdd(&hist[e], 1);
+  }
+  if (probs) {
+    const int groups = 256 / E, grp = threadIdx.x / E, e = threadIdx.x % E;
+    float sum = 0.0f;
+    if (grp < groups) {
+#pragma unroll 8
+      for (long t = t0 + grp; t < t1; t += groups) sum += probs[t * E + e];
+    }
+    part[threadIdx.x] = sum;
+    __syncthreads();
+    if (threadIdx.x < E) {
+      for (int gq = 1; gq < groups; ++gq) sum += part[gq * E + threadIdx.x];
+      colsum[(long)blockIdx.x * E + threadIdx.x] = sum;
+    }
   }
   __syncthreads();
   if (threadIdx.x < E) block_counts[(long)blockIdx.x * E + threadIdx.x] = hist[threadIdx.x];
 }
 
-// Fixed-order scan: offsets[e] (exclusive over experts), per-block bases.
-// One block of kMaxE threads.
-__global__ __launch_bounds__(256) void sort_scan_k(int32_t* __restrict__ block_counts, int nblk,
-                                                   int E, int32_t* __restrict__ counts,
-                                                   int32_t* __restrict__ offsets) {
-  __shared__ int tot[kMaxE];
-  const int e = threadIdx.x;
-  if (e < E) {
-    int run = 0;
-    for (int b = 0; b < nblk; ++b) {
-      const int c = block_counts[(long)b * E + e];
-      block_counts[(long)b * E + e] = run;  // becomes the in-expert base of block b
-      run += c;
+// Scan and scatter. Every block adds up the nblk histograms itself (coalesced,
+// all loads in flight; at most kSortBlocks of them, from L2), which takes the
+// place of a one-block scan launch between the two kernels (16 us at 64 blocks
+// of 64 experts, a chain of dependent loads); block 0 writes counts and
+// offsets (and, with colsum, adds the load-balance loss to aux). Then eight
+// waves share the block's entries in flat order: each counts its own, the
+// waves' bases follow in wave order, and each walks its entries 64 at a time:
+// the lanes holding the same expert are found with one ballot per bit of the
+// expert id (E <= 256: eight bits), so each lane's rank among the earlier
+// lanes of its expert is a popcount, and the group's lowest lane advances the
+// expert's running position. Entries outside [0, E) are skipped.
+// perm[pos] = flat entry, pos_of[flat entry] = pos.
+constexpr int kScatterWaves = 8;
+__global__ __launch_bounds__(64 * kScatterWaves) void sort_scatter_k(
+    const int32_t* __restrict__ idx, int T, int E, int k, int tok, int nblk,
+    const int32_t* __restrict__ block_counts, int32_t* __restrict__ counts,
+    int32_t* __restrict__ offsets, int32_t* __restrict__ perm, int32_t* __restrict__ pos_of,
+    const float* __restrict__ colsum, float alpha, float* __restrict__ aux) {
+  constexpr int NT = 64 * kScatterWaves;
+  __shared__ int tot[NT], pre[NT], off[kMaxE];
+  __shared__ int run[kScatterWaves][kMaxE];
+  __shared__ float fpart[NT];
+  __shared__ float term[kScatterWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int groups = NT / E, grp = tid / E, ge = tid % E;
+  const int me = blockIdx.x;
+  int all = 0, before = 0;
+  if (grp < groups) {
+#pragma unroll 8
+    for (int b = grp; b < nblk; b += groups) {
+      const int c = block_counts[(long)b * E + ge];
+      all += c;
+      before += b < me ? c : 0;
     }
-    tot[e] = run;
-    counts[e] = run;
+  }
+  tot[tid] = all;
+  pre[tid] = before;
+  for (int i = tid; i < kScatterWaves * kMaxE; i += NT) (&run[0][0])[i] = 0;
+  __syncthreads();
+  if (tid < E) {
+    for (int gq = 1; gq < groups; ++gq) {
+      all += tot[gq * E + tid];
+      before += pre[gq * E + tid];
+    }
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int acc = 0;
-    for (int i = 0; i < E; ++i) {
-      offsets[i] = acc;
-      acc += tot[i];
-    }
-    offsets[E] = acc;
+  if (tid < kMaxE) {
+    tot[tid] = tid < E ? all : 0;
+    pre[tid] = before;
   }
-}
-
-// Ranks within each expert in flat order: one wave per block, 64 entries per
-// round; for each expert present in the round, a ballot gives the lanes'
-// ranks. perm[pos] = flat entry, pos_of[flat entry] = pos.
-__global__ __launch_bounds__(64) void sort_scatter_k(const int32_t* __restrict__ idx, int T, int E,
-                                                     int k, const int32_t* __restrict__ block_base,
-                                                     const int32_t* __restrict__ offsets,
-                                                     int32_t* __restrict__ perm,
-                                                     int32_t* __restrict__ pos_of) {
-  // One wave walks the block's entries 64 at a time in flat order. The lanes
-  // holding the same expert are found with one ballot per bit of the expert
-  // id (E <= 256: eight bits), so each lane's rank among the earlier lanes of
-  // its expert is a popcount, and the group's lowest lane advances the
-  // expert's running position. Entries outside [0, E) are skipped.
-  __shared__ int run[kMaxE];
-  const int lane = threadIdx.x;
-  for (int e = lane; e < E; e += 64)
-    run[e] = offsets[e] + block_base[(long)blockIdx.x * E + e];
+  // each wave's own histogram (entries of a wave: whole rounds of 64)
+  const long f0 = (long)me * tok * k, f1 = min((long)T * k, f0 + (long)tok * k);
+  const long per = ((f1 - f0 + kScatterWaves * 64 - 1) / (kScatterWaves * 64)) * 64;
+  const long w0 = min(f1, f0 + wave * per), w1 = min(f1, w0 + per);
+  for (long f = w0 + lane; f < w1; f += 64) {
+    const int e = idx[f];
+    if ((unsigned)e < (unsigned)E) atomicAdd(&run[wave][e], 1);
+  }
   __syncthreads();
-  const long f0 = (long)blockIdx.x * kSortTokens * k;
-  const long f1 = min((long)T * k, f0 + (long)kSortTokens * k);
+  if (wave == 0) {  // exclusive scan over the experts, four to a lane
+    int c[4], s = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      c[i] = tot[lane * 4 + i];
+      s += c[i];
+    }
+    int incl = s;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int u = __shfl_up(incl, d, 64);
+      if (lane >= d) incl += u;
+    }
+    int at = incl - s;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      off[lane * 4 + i] = at;
+      at += c[i];
+    }
+  }
+  __syncthreads();
+  if (tid < E) {
+    int at = off[tid] + pre[tid];
+#pragma unroll
+    for (int w = 0; w < kScatterWaves; ++w) {
+      const int n = run[w][tid];
+      run[w][tid] = at;
+      at += n;
+    }
+    if (me == 0) {
+      counts[tid] = tot[tid];
+      offsets[tid] = off[tid];
+      if (tid == E - 1) offsets[E] = off[tid] + tot[tid];
+    }
+  }
+  __syncthreads();
+  int* mine = run[wave];
   const uint64_t below = (1ull << lane) - 1ull;
-  for (long base = f0; base < f1; base += 64) {
+  for (long base = w0; base < w1; base += 64) {
     const long f = base + lane;
-    const int raw = f < f1 ? idx[f] : -1;
+    const int raw = f < w1 ? idx[f] : -1;
     const bool ok = (unsigned)raw < (unsigned)E;
     const int e = ok ? raw : 0;
     uint64_t same = __ballot(ok);
@@ -187,14 +280,32 @@ __global__ __launch_bounds__(64) void sort_scatter_k(const int32_t* __restrict__
       const uint64_t ones = __ballot(ok && ((e >> b) & 1));
       same &= ((e >> b) & 1) ? ones : ~ones;
     }
-    const int pos = run[e] + __popcll(same & below);  // every lane reads before any update
+    const int pos = mine[e] + __popcll(same & below);  // every lane reads before any update
     __builtin_amdgcn_wave_barrier();
     if (ok) {
       perm[pos] = (int32_t)f;
       pos_of[f] = pos;
-      if ((same & below) == 0) run[e] += __popcll(same);
+      if ((same & below) == 0) mine[e] += __popcll(same);
     }
     __builtin_amdgcn_wave_barrier();
+  }
+  // aux += alpha E sum_e f_e P_e with P_e = sum_t p[t, e] / T
+  if (me == 0 && colsum) {
+    float c = 0.0f;
+    if (grp < groups) {
+#pragma unroll 8
+      for (int b = grp; b < nblk; b += groups) c += colsum[(long)b * E + ge];
+    }
+    fpart[tid] = c;
+    __syncthreads();
+    if (tid < E)
+      for (int gq = 1; gq < groups; ++gq) c += fpart[gq * E + tid];
+    const float fe = tid < E ? (float)tot[tid] / ((float)T * k) : 0.0f;
+    const float w = wave_sum(tid < E ? fe * c : 0.0f);
+    if (lane == 0) term[wave] = w;
+    __syncthreads();
+    if (tid == 0)
+      aux[0] += alpha * (float)E * ((term[0] + term[1]) + (term[2] + term[3])) / (float)T;
   }
 }
 
@@ -224,6 +335,7 @@ __global__ __launch_bounds__(256) void combine_k(const bf16_t* __restrict__ ys,
   const long t = id / cpr;
   const int c = (int)(id % cpr);
   float acc[8] = {};
+#pragma unroll 4
   for (int j = 0; j < k; ++j) {
     const float g = gates[t * k + j];
     float y[8];
@@ -298,6 +410,7 @@ __global__ __launch_bounds__(256) void scatter_back_k(const bf16_t* __restrict__
   const long t = id / cpr;
   const int c = (int)(id % cpr);
   float acc[8] = {};
+#pragma unroll 4
   for (int j = 0; j < k; ++j) {
     float y[8];
     unpack8(reinterpret_cast<const uint4*>(dxs + (long)pos_of[t * k + j] * h)[c], y);
@@ -307,44 +420,12 @@ __global__ __launch_bounds__(256) void scatter_back_k(const bf16_t* __restrict__
   reinterpret_cast<uint4*>(db + t * h)[c] = pack8(acc);
 }
 
-// Column sums of the router probabilities over kAuxTokens-token blocks,
-// partial[block][e] (thread e sums its expert's column in token order);
-// aux_loss_k adds the blocks in block order: P_e = sum_t p[t, e], and
-// aux += alpha E sum_e f_e P_e / T.
-constexpr int kAuxTokens = 64;
-__global__ __launch_bounds__(256) void prob_colsum_k(const float* __restrict__ probs, int T, int E,
-                                                     float* __restrict__ partial) {
-  const int e = threadIdx.x;
-  const long t0 = (long)blockIdx.x * kAuxTokens;
-  const long t1 = min((long)T, t0 + kAuxTokens);
-  if (e >= E) return;
-  float sum = 0.0f;
-  for (long t = t0; t < t1; ++t) sum += probs[t * E + e];
-  partial[(long)blockIdx.x * E + e] = sum;
-}
-
-__global__ __launch_bounds__(256) void aux_loss_k(const float* __restrict__ partial, int nblk,
-                                                  const int32_t* __restrict__ counts, int T, int E,
-                                                  int k, float alpha, float* __restrict__ colsum,
-                                                  float* __restrict__ aux) {
-  __shared__ float part[4];
-  const int e = threadIdx.x;
-  float c = 0.0f;
-  if (e < E)
-    for (int b = 0; b < nblk; ++b) c += partial[(long)b * E + e];
-  if (e < E) colsum[e] = c;
-  const float fe = e < E ? (float)counts[e] / ((float)T * k) : 0.0f;
-  const float term = wave_sum(fe * c);
-  if ((e & 63) == 0) part[e >> 6] = term;
-  __syncthreads();
-  if (e == 0 && aux) aux[0] += alpha * (float)E * ((part[0] + part[1]) + (part[2] + part[3])) /
-                               (float)T;
-}
-
 // dl[t, e] = p (dp - sum_e p dp) with dp = dgate on chosen experts plus the
 // aux term alpha E f_e / T on every expert; written as bf16 for the router
 // data / weight gradient products. One wave per token, lane l holding
-// experts l + 64 i.
+// experts l + 64 i; lane j loads choice j, and the choices are then read from
+// its registers (k <= 64).
+template <int NS>
 __global__ __launch_bounds__(256) void router_bwd_k(const float* __restrict__ probs,
                                                     const int32_t* __restrict__ idx,
                                                     const float* __restrict__ dgate,
@@ -354,20 +435,27 @@ __global__ __launch_bounds__(256) void router_bwd_k(const float* __restrict__ pr
   const int lane = threadIdx.x & 63;
   const long t = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= T) return;
-  float p[kSlots], dp[kSlots];
+  const int my_e = lane < k ? idx[t * k + lane] : -1;
+  const int my_d = lane < k ? __float_as_int(dgate[t * k + lane]) : 0;
+  float p[NS], dp[NS];
   float part = 0.0f;
 #pragma unroll
-  for (int i = 0; i < kSlots; ++i) {
+  for (int i = 0; i < NS; ++i) {
     const int e = lane + 64 * i;
     p[i] = e < E ? probs[t * E + e] : 0.0f;
     dp[i] = e < E ? alpha * (float)E * ((float)counts[e] / ((float)T * k)) / (float)T : 0.0f;
-    for (int j = 0; j < k; ++j)
-      if (idx[t * k + j] == e) dp[i] += dgate[t * k + j];
-    part += p[i] * dp[i];
   }
+  for (int j = 0; j < k; ++j) {
+    const int e = __builtin_amdgcn_readlane(my_e, j);
+    const float d = __int_as_float(__builtin_amdgcn_readlane(my_d, j));
+#pragma unroll
+    for (int i = 0; i < NS; ++i) dp[i] += lane + 64 * i == e ? d : 0.0f;
+  }
+#pragma unroll
+  for (int i = 0; i < NS; ++i) part += p[i] * dp[i];
   const float dot = wave_sum(part);
 #pragma unroll
-  for (int i = 0; i < kSlots; ++i) {
+  for (int i = 0; i < NS; ++i) {
     const int e = lane + 64 * i;
     if (e < E) dl[t * E + e] = f2bf(p[i] * (dp[i] - dot));
   }
@@ -377,23 +465,41 @@ inline unsigned nblocks(long work, int threads) { return (unsigned)((work + thre
 
 }  // namespace
 
-int moe_sort_blocks(int T) { return (T + kSortTokens - 1) / kSortTokens; }
+namespace {
+// tokens of a counting-sort block: every block reads every block's histogram,
+// so their number is bounded
+int sort_tokens(int T) {
+  const long most = (long)kSortTokens * kSortBlocks;
+  return kSortTokens * (int)(((long)T + most - 1) / most);
+}
+}  // namespace
+
+int moe_sort_blocks(int T) {
+  const int tok = sort_tokens(T);
+  return (int)(((long)T + tok - 1) / tok);
+}
 
 hipError_t moe_route(const float* logits, int T, int E, int k, int32_t* idx, float* gates,
                      float* probs, hipStream_t s) {
   if (T <= 0) return hipSuccess;
-  hipLaunchKernelGGL(route_k, dim3(nblocks(T, 4)), dim3(256), 0, s, logits, T, E, k, idx, gates, probs);
+  const dim3 grid(nblocks(T, 4)), block(256);
+  if (E <= 64) hipLaunchKernelGGL(route_k<1>, grid, block, 0, s, logits, T, E, k, idx, gates, probs);
+  else if (E <= 128) hipLaunchKernelGGL(route_k<2>, grid, block, 0, s, logits, T, E, k, idx, gates, probs);
+  else if (E <= 192) hipLaunchKernelGGL(route_k<3>, grid, block, 0, s, logits, T, E, k, idx, gates, probs);
+  else hipLaunchKernelGGL(route_k<4>, grid, block, 0, s, logits, T, E, k, idx, gates, probs);
   return hipGetLastError();
 }
 
 hipError_t moe_sort(const int32_t* idx, int T, int E, int k, int32_t* block_counts,
                     int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* pos_of,
-                    hipStream_t s) {
-  const int nb = moe_sort_blocks(T);
-  hipLaunchKernelGGL(sort_count_k, dim3(nb), dim3(256), 0, s, idx, T, E, k, block_counts);
-  hipLaunchKernelGGL(sort_scan_k, dim3(1), dim3(kMaxE), 0, s, block_counts, nb, E, counts, offsets);
-  hipLaunchKernelGGL(sort_scatter_k, dim3(nb), dim3(64), 0, s, idx, T, E, k, block_counts, offsets,
-                     perm, pos_of);
+                    hipStream_t s, const float* probs, float alpha, float* colsum, float* aux) {
+  if (T <= 0) return hipSuccess;
+  const int nb = moe_sort_blocks(T), tok = sort_tokens(T);
+  if (!aux) probs = colsum = nullptr;
+  hipLaunchKernelGGL(sort_count_k, dim3(nb), dim3(256), 0, s, idx, T, E, k, tok, block_counts,
+                     probs, colsum);
+  hipLaunchKernelGGL(sort_scatter_k, dim3(nb), dim3(64 * kScatterWaves), 0, s, idx, T, E, k, tok,
+                     nb, block_counts, counts, offsets, perm, pos_of, colsum, alpha, aux);
   return hipGetLastError();
 }
 
@@ -427,23 +533,18 @@ hipError_t moe_scatter_back(const uint16_t* dxs, const int32_t* pos_of, long T, 
   return hipGetLastError();
 }
 
-int moe_aux_blocks(int T) { return (T + kAuxTokens - 1) / kAuxTokens; }
-hipError_t moe_aux_loss(const float* probs, const int32_t* counts, int T, int E, int k, float alpha,
-                        float* colsum, float* aux, hipStream_t s) {
-  // colsum holds E sums followed by moe_aux_blocks(T) * E block partials
-  if (T <= 0) return hipSuccess;
-  const int nb = moe_aux_blocks(T);
-  float* partial = colsum + E;
-  hipLaunchKernelGGL(prob_colsum_k, dim3(nb), dim3(256), 0, s, probs, T, E, partial);
-  hipLaunchKernelGGL(aux_loss_k, dim3(1), dim3(256), 0, s, partial, nb, counts, T, E, k, alpha, colsum, aux);
-  return hipGetLastError();
-}
-
 hipError_t moe_router_bwd(const float* probs, const int32_t* idx, const float* dgate,
                           const int32_t* counts, int T, int E, int k, float alpha, uint16_t* dl,
                           hipStream_t s) {
   if (T <= 0) return hipSuccess;
-  hipLaunchKernelGGL(router_bwd_k, dim3(nblocks(T, 4)), dim3(256), 0, s, probs, idx, dgate, counts, T, E, k, alpha, dl);
+  const dim3 grid(nblocks(T, 4)), block(256);
+#define FORGE_ROUTER_BWD(NS) \
+  hipLaunchKernelGGL(router_bwd_k<NS>, grid, block, 0, s, probs, idx, dgate, counts, T, E, k, alpha, dl)
+  if (E <= 64) FORGE_ROUTER_BWD(1);
+  else if (E <= 128) FORGE_ROUTER_BWD(2);
+  else if (E <= 192) FORGE_ROUTER_BWD(3);
+  else FORGE_ROUTER_BWD(4);
+#undef FORGE_ROUTER_BWD
   return hipGetLastError();
 }
 
