@@ -194,7 +194,8 @@ forge_status forge_layer_saved_bytes(const forge_layer_cfg* cfg, size_t* bytes);
  * bf16 for t = ceil(seq / 64) 64-key tiles (the causal half of each head's
  * seq x seq score gradient; 545 MB at 32 heads and seq 4096), and, for layers
  * whose products have few output tiles, up to 2 x 64 MB of fp32 partial
- * products. */
+ * products, and the partial sums described at
+ * forge_attention_bwd_workspace_bytes. */
 forge_status forge_layer_workspace_bytes(const forge_layer_cfg* cfg, size_t* bytes);
 
 /* Items of a MoE layer's saved buffer that forge_layer_saved_item locates:
@@ -591,8 +592,10 @@ forge_status forge_attention_fwd(const forge_attn_cfg* cfg, const forge_bf16* qk
                                  forge_bf16* o, float* lse, forge_stream stream);
 
 /* Scratch bytes of forge_attention_bwd: 2 * batch * n_heads * seq fp32
- * (per-query -rowsum(dO o) and -lse log2 e) and the dS scratch described at
- * forge_layer_workspace_bytes, each rounded up to 256 bytes. Host only. */
+ * (per-query -rowsum(dO o) and -lse log2 e), the dS scratch described at
+ * forge_layer_workspace_bytes and, where there are few 64-key tiles x kv heads,
+ * fp32 partial sums of dk and dv (at most 64 MB), each rounded up to 256
+ * bytes. Host only. */
 forge_status forge_attention_bwd_workspace_bytes(const forge_attn_cfg* cfg, size_t* bytes);
 
 /*

@@ -589,9 +589,32 @@ struct KvBuf {
   static constexpr int DMA = 2 * P::PER + 1;
   static constexpr int ARR = 4 * WBUF > 2 * P::RED ? 4 * WBUF : 2 * P::RED;
 };
+// Key tile, batch row, kv head and split of a key-owned block: kv head fastest,
+// key tile slowest.
+struct KvBlock {
+  int kt, b, m, z;
+  __device__ __forceinline__ KvBlock(const AttnArgs& a, int splits) {
+    const int per_kt = a.n_kv_heads * a.batch * splits;
+    kt = (int)blockIdx.x / per_kt;
+    const int r = (int)blockIdx.x % per_kt;
+    m = r % a.n_kv_heads;
+    b = r / a.n_kv_heads % a.batch;
+    z = r / a.n_kv_heads / a.batch;
+  }
+};
 // s_waitcnt immediate that waits for vmcnt <= n only (gfx9 encoding: vmcnt
 // bits 3:0 and 15:14, expcnt 6:4 and lgkmcnt 11:8 at their maxima)
 constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
+
+// The block's rows of its split's partial sums [splits][T][n_kv * D] (NULL
+// when the pairs are not split).
+template <int D>
+__device__ __forceinline__ float* kv_part(const AttnArgs& a, float* part, const KvBlock& k,
+                                          long row) {
+  if (!part) return nullptr;
+  const long T = (long)a.batch * a.seq;
+  return part + ((k.z * T + row) * a.n_kv_heads + k.m) * D;
+}
 
 template <int D>
 __device__ __forceinline__ void slab_offsets(long ld, int lane, uint32_t (&off)[KvPlan<D>::PER]) {
@@ -617,11 +640,14 @@ __device__ __forceinline__ void dma_slab(const bf16_t* base, long ld, int row0, 
 
 // The four waves' [64 keys][D] accumulators (acc[db][kb]: rows d, columns
 // keys) summed in wave order through sm0 / sm1, times scale, stored as bf16
-// rows out[key][D] (key-major, row stride ld) for the first nkeys keys.
+// rows out[key][D] (key-major, row stride ld) for the first nkeys keys; with
+// part (a block that holds one split of the pairs) as fp32 rows part[key][D]
+// (row stride ldp), unscaled.
 template <int D>
 __device__ __forceinline__ void kv_reduce_store(const f32x16_t (&acc)[D / 32][2], uint4* sm0,
                                                 uint4* sm1, int wave, int lane, float scale,
-                                                bf16_t* out, long ld, int nkeys) {
+                                                bf16_t* out, long ld, float* part, long ldp,
+                                                int nkeys) {
   using P = KvPlan<D>;
   constexpr int DB = D / 32;
   const int hh = lane >> 5, l32 = lane & 31;
@@ -639,22 +665,29 @@ __device__ __forceinline__ void kv_reduce_store(const f32x16_t (&acc)[D / 32][2]
                         acc[db][kb][g * 4 + 3]);
   __syncthreads();
   // the four threads of a key take interleaved 8-column pieces (columns
-  // 32 j + 8 part ..), so eight lanes of a 16-byte read cover all banks
+  // 32 j + 8 piece ..), so eight lanes of a 16-byte read cover all banks
   const int key = threadIdx.x >> 2;
-  const int part = threadIdx.x & 3;
+  const int piece = threadIdx.x & 3;
   if (key < nkeys) {
     const float* w0 = reinterpret_cast<const float*>(sm0);
     const float* w1 = reinterpret_cast<const float*>(sm0 + P::RED);
     const float* w2 = reinterpret_cast<const float*>(sm1);
     const float* w3 = reinterpret_cast<const float*>(sm1 + P::RED);
-    bf16_t* orow = out + (long)key * ld + part * 8;
 #pragma unroll
     for (int j = 0; j < D / 32; ++j) {
-      const int o = key * (D + 4) + j * 32 + part * 8;
+      const int o = key * (D + 4) + j * 32 + piece * 8;
       float f[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) f[u] = (((w0[o + u] + w1[o + u]) + w2[o + u]) + w3[o + u]) * scale;
-      *reinterpret_cast<uint4*>(orow + j * 32) = pack8(f);
+      for (int u = 0; u < 8; ++u) f[u] = ((w0[o + u] + w1[o + u]) + w2[o + u]) + w3[o + u];
+      if (part) {
+        float4* prow = reinterpret_cast<float4*>(part + (long)key * ldp + piece * 8 + j * 32);
+        prow[0] = make_float4(f[0], f[1], f[2], f[3]);
+        prow[1] = make_float4(f[4], f[5], f[6], f[7]);
+      } else {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) f[u] *= scale;
+        *reinterpret_cast<uint4*>(out + (long)key * ld + piece * 8 + j * 32) = pack8(f);
+      }
     }
   }
 }
@@ -669,7 +702,8 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dv_k(AttnArgs a,
                                                        const bf16_t* __restrict__ dout,
                                                        const float* __restrict__ delta,
                                                        bf16_t* __restrict__ ds,
-                                                       bf16_t* __restrict__ dv, long ld_d) {
+                                                       bf16_t* __restrict__ dv, long ld_d,
+                                                       float* __restrict__ part, int splits) {
   using P = KvPlan<D>;
   using B = KvBuf<D>;
   constexpr int BK = P::BK, BQ = P::BQ, SLAB = P::SLAB, KK = D / 16, DB = D / 32;
@@ -680,10 +714,8 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dv_k(AttnArgs a,
   const int grp = a.n_heads / a.n_kv_heads;
   // block order: key tile slowest, so the low key tiles (the most work)
   // are dispatched first
-  const int per_kt = a.n_kv_heads * a.batch;
-  const int kt = (int)blockIdx.x / per_kt;
-  const int m = (int)blockIdx.x % per_kt % a.n_kv_heads;
-  const int b = (int)blockIdx.x % per_kt / a.n_kv_heads;
+  const KvBlock kb_(a, splits);
+  const int kt = kb_.kt, m = kb_.m, b = kb_.b;
   const int k0 = kt * BK;
   const int j0 = k0 / BQ;                      // first slab holding a query >= k0
   const int ns = (S + BQ - 1) / BQ - j0;       // slabs per query head
@@ -869,16 +901,17 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dv_k(AttnArgs a,
   // leave the other buffer's DMA in flight.
   uint4* my0 = sm0 + wave * B::WBUF;
   uint4* my1 = sm1 + wave * B::WBUF;
-  load(min(wave, total - 1), my0);
-  for (int p = wave; p < total; p += 8) {
-    load(min(p + 4, total - 1), my1);
+  const int p0 = wave + 4 * kb_.z, step = 4 * splits;
+  load(min(p0, total - 1), my0);
+  for (int p = p0; p < total; p += 2 * step) {
+    load(min(p + step, total - 1), my1);
     pair(my0, p);
-    if (p + 4 >= total) break;
-    load(min(p + 8, total - 1), my0);
-    pair(my1, p + 4);
+    if (p + step >= total) break;
+    load(min(p + 2 * step, total - 1), my0);
+    pair(my1, p + step);
   }
-  kv_reduce_store<D>(acc, sm0, sm1, wave, lane, 1.0f, dv + (rb + k0) * ld_d + (long)m * D,
-                             ld_d, S - k0);
+  kv_reduce_store<D>(acc, sm0, sm1, wave, lane, 1.0f, dv + (rb + k0) * ld_d + (long)m * D, ld_d,
+                     kv_part<D>(a, part, kb_, rb + k0), (long)a.n_kv_heads * D, S - k0);
 }
 
 // 3. dK pass: dK^T += Q^T dS over the block's pairs. Each pair's Q slab and
@@ -899,7 +932,8 @@ struct DkPlan {
 
 template <int D>
 __global__ __launch_bounds__(256, 1) void attn_bwd_dk_k(AttnArgs a, const bf16_t* __restrict__ ds,
-                                                       bf16_t* __restrict__ dk, long ld_d) {
+                                                       bf16_t* __restrict__ dk, long ld_d,
+                                                       float* __restrict__ part, int splits) {
   using P = KvPlan<D>;
   using R = DkPlan<D>;
   constexpr int BK = P::BK, BQ = P::BQ, KK = D / 16, DB = D / 32, KR = R::KR;
@@ -908,10 +942,8 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dk_k(AttnArgs a, const bf16_t
 
   const int S = a.seq;
   const int grp = a.n_heads / a.n_kv_heads;
-  const int per_kt = a.n_kv_heads * a.batch;
-  const int kt = (int)blockIdx.x / per_kt;
-  const int m = (int)blockIdx.x % per_kt % a.n_kv_heads;
-  const int b = (int)blockIdx.x % per_kt / a.n_kv_heads;
+  const KvBlock kb_(a, splits);
+  const int kt = kb_.kt, m = kb_.m, b = kb_.b;
   const int k0 = kt * BK;
   const int j0 = k0 / BQ;
   const int ns = (S + BQ - 1) / BQ - j0;
@@ -998,28 +1030,58 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dk_k(AttnArgs a, const bf16_t
     __builtin_amdgcn_sched_barrier(0);
   };
 
-  // The wave's pairs p = wave + 4 i; pair i sits in slot i % KR. Every step
+  // The wave's pairs p = p0 + step i; pair i sits in slot i % KR. Every step
   // issues the same number of DMA instructions (past the last pair it
   // reloads the last pair, unused), so the wait count above is exact.
+  const int p0 = wave + 4 * kb_.z, step = 4 * splits;
 #pragma unroll
-  for (int u = 0; u < KR - 1; ++u) load(min(wave + 4 * u, total - 1), u);
+  for (int u = 0; u < KR - 1; ++u) load(min(p0 + step * u, total - 1), u);
   bool done = false;
-  for (int p = wave; !done; p += 4 * KR) {
+  for (int p = p0; !done; p += step * KR) {
 #pragma unroll
     for (int u = 0; u < KR; ++u) {
       if (!done) {
-        const int pp = p + 4 * u;
+        const int pp = p + step * u;
         if (pp >= total) {
           done = true;
         } else {
-          load(min(pp + 4 * (KR - 1), total - 1), (u + KR - 1) % KR);
+          load(min(pp + step * (KR - 1), total - 1), (u + KR - 1) % KR);
           pair(u);
         }
       }
     }
   }
   kv_reduce_store<D>(acc, sm, sm + 2 * P::RED, wave, lane, a.scale,
-                     dk + (rb + k0) * ld_d + (long)m * D, ld_d, S - k0);
+                     dk + (rb + k0) * ld_d + (long)m * D, ld_d,
+                     kv_part<D>(a, part, kb_, rb + k0), (long)a.n_kv_heads * D, S - k0);
+}
+
+// dK and dV from the splits' partial sums, added in split order; eight columns
+// per thread, grid.y 0: dK (times scale), 1: dV.
+__global__ __launch_bounds__(256) void attn_bwd_kv_sum_k(const float* __restrict__ pk,
+                                                         const float* __restrict__ pv, int splits,
+                                                         long rows, int width, float scale,
+                                                         bf16_t* __restrict__ dk,
+                                                         bf16_t* __restrict__ dv, long ld_d) {
+  const int cpr = width / 8;
+  const long q = (long)blockIdx.x * 256 + threadIdx.x;
+  if (q >= rows * cpr) return;
+  const long r = q / cpr;
+  const int c = (int)(q % cpr) * 8;
+  const bool v = blockIdx.y != 0;
+  const float* src = (v ? pv : pk) + r * width + c;
+  const long stride = rows * width;
+  f32x4_t x = *reinterpret_cast<const f32x4_t*>(src);
+  f32x4_t y = *reinterpret_cast<const f32x4_t*>(src + 4);
+#pragma unroll 4
+  for (int z = 1; z < splits; ++z) {
+    x += *reinterpret_cast<const f32x4_t*>(src + z * stride);
+    y += *reinterpret_cast<const f32x4_t*>(src + z * stride + 4);
+  }
+  const float sc = v ? 1.0f : scale;
+  const float f[8] = {x[0] * sc, x[1] * sc, x[2] * sc, x[3] * sc,
+                      y[0] * sc, y[1] * sc, y[2] * sc, y[3] * sc};
+  *reinterpret_cast<uint4*>((v ? dv : dk) + r * ld_d + c) = pack8(f);
 }
 
 // 4. dQ: block of 256 queries (32 per wave, eight waves) of one (batch,
@@ -1201,31 +1263,60 @@ size_t attn_bwd_ds_bytes(const AttnArgs& a) {
   return (size_t)a.batch * a.n_heads * DsLayout(a.seq).head * 2;
 }
 
-hipError_t attn_bwd(const AttnArgs& a, const uint16_t* o, const uint16_t* dout, const float* lse,
-                    float* delta, uint16_t* ds, uint16_t* dq, uint16_t* dk, uint16_t* dv,
-                    long ld_d, hipStream_t s) {
-  const long rows = (long)a.batch * a.seq * a.n_heads;
+// Splits of a key-owned block's pairs. One block per 64 keys of a kv head
+// leaves CUs idle on short sequences with few kv heads (32 blocks at 1000
+// tokens and 2 kv heads), and below about 512 blocks the first key tile, with
+// twice the average work, is what the launch takes; splitting the pairs of a
+// block towards 512 blocks evens both out, for fp32 partial sums of dK and dV
+// that one more launch adds up. A wave keeps at least two pairs of the longest
+// block, and short launches (fewer than four) stay whole.
+static int kv_splits(const AttnArgs& a) {
+  const long blocks = (long)((a.seq + 63) / 64) * a.n_kv_heads * a.batch;
+  const long pairs = (long)(a.n_heads / a.n_kv_heads) * ((a.seq + 31) / 32);
+  long z = (512 + blocks - 1) / blocks;
+  z = z < pairs / 8 ? z : pairs / 8;
+  z = z < 16 ? z : 16;
+  return pairs < 16 || z < 2 ? 1 : (int)z;
+}
+
+size_t attn_bwd_part_bytes(const AttnArgs& a) {
+  const int z = kv_splits(a);
+  return z > 1 ? (size_t)2 * z * a.batch * a.seq * a.n_kv_heads * a.d * 4 : 0;
+}
+
+namespace {
+template <int D>
+hipError_t attn_bwd_d(const AttnArgs& a, const uint16_t* o, const uint16_t* dout, const float* lse,
+                      float* delta, uint16_t* ds, float* part, uint16_t* dq, uint16_t* dk,
+                      uint16_t* dv, long ld_d, hipStream_t s) {
+  const long T = (long)a.batch * a.seq, rows = T * a.n_heads;
+  const int z = kv_splits(a), width = a.n_kv_heads * D;
+  float* pk = z > 1 ? part : nullptr;
+  float* pv = z > 1 ? part + (long)z * T * width : nullptr;
   const dim3 block(256);
-  const dim3 kgrid((unsigned)((a.seq + 63) / 64 * a.n_kv_heads * a.batch));
+  const dim3 pgrid((unsigned)((rows + 2048 / D - 1) / (2048 / D)));
+  const dim3 kgrid((unsigned)((long)((a.seq + 63) / 64) * a.n_kv_heads * a.batch * z));
   const dim3 qgrid((unsigned)((a.seq + 255) / 256 * a.n_heads * a.batch));
-  if (a.d == 128) {
-    const dim3 pgrid((unsigned)((rows + 15) / 16));
-    hipLaunchKernelGGL(attn_bwd_prep_k<128>, pgrid, block, 0, s, o, dout, lse, delta, rows,
-                       a.n_heads, a.seq);
-    hipLaunchKernelGGL(attn_bwd_dv_k<128>, kgrid, block, 0, s, a, dout, delta, ds, dv, ld_d);
-    hipLaunchKernelGGL(attn_bwd_dk_k<128>, kgrid, block, 0, s, a, ds, dk, ld_d);
-    hipLaunchKernelGGL(attn_bwd_dq_k<128>, qgrid, dim3(512), 0, s, a, ds, dq, ld_d);
-  } else if (a.d == 64) {
-    const dim3 pgrid((unsigned)((rows + 31) / 32));
-    hipLaunchKernelGGL(attn_bwd_prep_k<64>, pgrid, block, 0, s, o, dout, lse, delta, rows,
-                       a.n_heads, a.seq);
-    hipLaunchKernelGGL(attn_bwd_dv_k<64>, kgrid, block, 0, s, a, dout, delta, ds, dv, ld_d);
-    hipLaunchKernelGGL(attn_bwd_dk_k<64>, kgrid, block, 0, s, a, ds, dk, ld_d);
-    hipLaunchKernelGGL(attn_bwd_dq_k<64>, qgrid, dim3(512), 0, s, a, ds, dq, ld_d);
-  } else {
-    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(attn_bwd_prep_k<D>, pgrid, block, 0, s, o, dout, lse, delta, rows, a.n_heads,
+                     a.seq);
+  hipLaunchKernelGGL(attn_bwd_dv_k<D>, kgrid, block, 0, s, a, dout, delta, ds, dv, ld_d, pv, z);
+  hipLaunchKernelGGL(attn_bwd_dk_k<D>, kgrid, block, 0, s, a, ds, dk, ld_d, pk, z);
+  if (z > 1) {
+    const dim3 sgrid((unsigned)((T * (width / 8) + 255) / 256), 2);
+    hipLaunchKernelGGL(attn_bwd_kv_sum_k, sgrid, block, 0, s, pk, pv, z, T, width, a.scale, dk, dv,
+                       ld_d);
   }
+  hipLaunchKernelGGL(attn_bwd_dq_k<D>, qgrid, dim3(512), 0, s, a, ds, dq, ld_d);
   return hipGetLastError();
+}
+}  // namespace
+
+hipError_t attn_bwd(const AttnArgs& a, const uint16_t* o, const uint16_t* dout, const float* lse,
+                    float* delta, uint16_t* ds, float* part, uint16_t* dq, uint16_t* dk,
+                    uint16_t* dv, long ld_d, hipStream_t s) {
+  if (a.d == 128) return attn_bwd_d<128>(a, o, dout, lse, delta, ds, part, dq, dk, dv, ld_d, s);
+  if (a.d == 64) return attn_bwd_d<64>(a, o, dout, lse, delta, ds, part, dq, dk, dv, ld_d, s);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace forge

@@ -194,7 +194,7 @@ Saved saved_layout(const forge_layer_cfg& c) {
 
 // ---- workspace -------------------------------------------------------------
 struct Work {
-  size_t dA, dgu, db, dh1, dO, delta, ds, dqkv, da, dg, o, lse;
+  size_t dA, dgu, db, dh1, dO, delta, ds, kvpart, dqkv, da, dg, o, lse;
   size_t logits, blk, colsum, dys, dxs, dgate, dl, dbs;  // MoE
   size_t qk_dg, h1s, dA_s, dgu_s, db1;  // QK-Norm; shared expert
   // partial products of split reductions: of the forward and the data
@@ -255,6 +255,7 @@ Work work_layout(const forge_layer_cfg& c) {
   w.dO = take(d.T * d.hq * 2);
   w.delta = take(2 * d.B * d.nh * d.S * 4);   // delta, then -lse log2(e)
   w.ds = take(forge::attn_bwd_ds_bytes(attn_args(d, nullptr)));   // dS, causal half
+  w.kvpart = take(forge::attn_bwd_part_bytes(attn_args(d, nullptr)));
   w.dqkv = take(d.T * d.qkv * 2);
   w.da = take(d.T * d.h * 2);
   w.dg = take((size_t)forge::rmsnorm_bwd_blocks((int)d.T) * d.h * 4);
@@ -584,8 +585,9 @@ forge_status attn_block_bwd(const forge_layer_cfg& c, const Dims& d,
   FORGE_HIP(gemm.here(forge::kKC, forge::kMC, forge::kStoreBF16,
                       scaled(gargs(dh1, d.h, w->w_o, d.hq, dO, d.hq, d.T, d.hq, d.h), d.bs), s));
   if (opt) FORGE_HIP(opt_update(opt, s, ws, opt->o->w_o, g->d_w_o, d.h * d.hq));
-  FORGE_HIP(forge::attn_bwd(aa, o, dO, lse, delta, at<uint16_t>(workspace, wk.ds), dqkv,
-                             dqkv + d.hq, dqkv + d.hq + d.hkv, d.qkv, s));
+  FORGE_HIP(forge::attn_bwd(aa, o, dO, lse, delta, at<uint16_t>(workspace, wk.ds),
+                            at<float>(workspace, wk.kvpart), dqkv, dqkv + d.hq,
+                            dqkv + d.hq + d.hkv, d.qkv, s));
   if (d.qkn) {
     // inverse RoPE and the QK-Norm backward in place; gain gradients
     float* qdg = at<float>(workspace, wk.qk_dg);
@@ -1660,7 +1662,8 @@ forge_status forge_attention_bwd_workspace_bytes(const forge_attn_cfg* cfg, size
   FORGE_CHECK(bytes != nullptr, FORGE_ERR_INVALID_ARG, "bytes is NULL");
   const Dims d = attn_dims(*cfg);
   *bytes = up(2 * (size_t)cfg->batch * cfg->n_heads * cfg->seq * 4) +
-           up(forge::attn_bwd_ds_bytes(attn_args(d, nullptr)));
+           up(forge::attn_bwd_ds_bytes(attn_args(d, nullptr))) +
+           up(forge::attn_bwd_part_bytes(attn_args(d, nullptr)));
   return ok();
 }
 
@@ -1678,8 +1681,10 @@ forge_status forge_attention_bwd(const forge_attn_cfg* cfg, const forge_bf16* qk
   const forge::AttnArgs aa = attn_args(d, qkv);
   hipStream_t s = (hipStream_t)stream;
   float* delta = static_cast<float*>(workspace);
-  uint16_t* ds = at<uint16_t>(workspace, up(2 * (size_t)cfg->batch * cfg->n_heads * cfg->seq * 4));
-  FORGE_HIP(forge::attn_bwd(aa, o, d_o, lse, delta, ds, d_qkv, d_qkv + d.hq,
+  const size_t ds_off = up(2 * (size_t)cfg->batch * cfg->n_heads * cfg->seq * 4);
+  uint16_t* ds = at<uint16_t>(workspace, ds_off);
+  float* part = at<float>(workspace, ds_off + up(forge::attn_bwd_ds_bytes(aa)));
+  FORGE_HIP(forge::attn_bwd(aa, o, d_o, lse, delta, ds, part, d_qkv, d_qkv + d.hq,
                             d_qkv + d.hq + d.hkv, d.qkv, s));
   return ok();
 }

@@ -20,6 +20,10 @@ CASES = [
     (3, 33, 2, 2, 64),
     (1, 1, 4, 1, 128),
     (1, 257, 16, 4, 64),
+    # few key tiles x kv heads: the key-owned backward splits each block's
+    # pairs (16 ways, a ragged tail; blocks whose splits have no pair)
+    (1, 1000, 16, 1, 128),
+    (2, 520, 8, 2, 64),
 ]
 
 
