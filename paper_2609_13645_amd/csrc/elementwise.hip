@@ -156,19 +156,20 @@ __global__ __launch_bounds__(512) void rmsnorm_bwd_k(
 }
 
 // dg[c] += sum_b part[b][c]: a block covers 64 columns as 16 groups of four
-// (16-byte loads); 16 stripes of threads each sum every 16th partial row,
-// then the 16 stripe sums of a column are added in stripe order (fixed, so
-// deterministic).
+// (16-byte loads); 64 stripes of threads each sum every 64th partial row, then
+// the stripe sums of a column are added sixteen at a time in stripe order, and
+// the four of those in order (fixed, so deterministic).
 template <bool ACC>
-__global__ __launch_bounds__(256) void dg_reduce_k(const float* __restrict__ part, int nblk,
-                                                   float* __restrict__ dg, int h) {
-  __shared__ float4 red[16][16];
+__global__ __launch_bounds__(1024) void dg_reduce_k(const float* __restrict__ part, int nblk,
+                                                    float* __restrict__ dg, int h) {
+  __shared__ float4 red[64][16];
+  __shared__ float quarter[4][64];
   const int cg = threadIdx.x & 15, stripe = threadIdx.x >> 4;
   const int col = blockIdx.x * 64 + cg * 4;
   float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   if (col < h) {
 #pragma unroll 8
-    for (int b = stripe; b < nblk; b += 16) {
+    for (int b = stripe; b < nblk; b += 64) {
       const float4 v = *reinterpret_cast<const float4*>(part + (long)b * h + col);
       s.x += v.x;
       s.y += v.y;
@@ -178,13 +179,20 @@ __global__ __launch_bounds__(256) void dg_reduce_k(const float* __restrict__ par
   }
   red[stripe][cg] = s;
   __syncthreads();
+  if (threadIdx.x < 256) {
+    const int c = threadIdx.x & 63, q = threadIdx.x >> 6;
+    const float* rf = reinterpret_cast<const float*>(&red[q * 16][0]);
+    float t = 0.0f;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) t += rf[w * 64 + c];
+    quarter[q][c] = t;
+  }
+  __syncthreads();
   if (threadIdx.x < 64) {
     const int c = blockIdx.x * 64 + threadIdx.x;
     if (c < h) {
-      const float* rf = reinterpret_cast<const float*>(&red[0][0]);
-      float t = 0.0f;
-#pragma unroll
-      for (int w = 0; w < 16; ++w) t += rf[w * 64 + threadIdx.x];
+      const float t = (quarter[0][threadIdx.x] + quarter[1][threadIdx.x]) +
+                      (quarter[2][threadIdx.x] + quarter[3][threadIdx.x]);
       dg[c] = ACC ? dg[c] + t : t;
     }
   }
@@ -300,7 +308,9 @@ __global__ __launch_bounds__(256) void qknorm_rope_fwd_k(
 // backward dx = r (g dn) - x r^3 sum(g dn x) / d; the gain gradients
 // sum_rows dn x r go to per-block partials [2][nblk][d] (q heads, then k
 // heads), each block summing a fixed set of rows in a fixed order.
-constexpr int kQkBlocks = 256;
+// (four blocks per CU: HBM-bound, one block's four waves had too few loads in
+// flight; 16384 tokens x 24 heads of 128 took 169 us, now 66)
+constexpr int kQkBlocks = 1024;
 template <int D>
 __global__ __launch_bounds__(256) void qknorm_rope_bwd_k(
     bf16_t* __restrict__ dqkv, long ld, const bf16_t* __restrict__ raw,
@@ -442,20 +452,30 @@ __global__ void embed_fwd_k(const int32_t* __restrict__ ids, const bf16_t* __res
   *reinterpret_cast<uint4*>(x + t * h + c * 8) = val;
 }
 
-__global__ void embed_bwd_k(const int32_t* __restrict__ ids, const bf16_t* __restrict__ dx,
-                            float* __restrict__ demb, int T, int h, int V, float scale) {
-  const int cpr = h / 8;
-  const long id = (long)blockIdx.x * blockDim.x + threadIdx.x;
+// dE[id] += scale * dx. A wave takes 512 columns of a token, lane l the columns
+// l, l + 64, ..: each atomic instruction adds 64 consecutive floats, two whole
+// 128-byte lines (eight consecutive columns per lane touched all sixteen lines
+// in each of its eight instructions: 2048 x 2048 took 112 us, now 19).
+__global__ __launch_bounds__(256) void embed_bwd_k(const int32_t* __restrict__ ids,
+                                                   const bf16_t* __restrict__ dx,
+                                                   float* __restrict__ demb, int T, int h, int V,
+                                                   float scale) {
+  const int lane = threadIdx.x & 63;
+  const int cpr = (h + 511) / 512;
+  const long id = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (id >= (long)T * cpr) return;
   const long t = id / cpr;
-  const int c = (int)(id % cpr);
+  const int c0 = (int)(id % cpr) * 512 + lane;
   const int v = ids[t];
   if (v < 0 || v >= V) return;
+  const bf16_t* src = dx + t * h;
   float f[8];
-  unpack8(*reinterpret_cast<const uint4*>(dx + t * h + c * 8), f);
-  float* dst = demb + (long)v * h + c * 8;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) unsafeAtomicAdd(dst + e, f[e] * scale);
+  for (int e = 0; e < 8; ++e) f[e] = c0 + e * 64 < h ? bf2f(src[c0 + e * 64]) : 0.0f;
+  float* dst = demb + (long)v * h;
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+    if (c0 + e * 64 < h) unsafeAtomicAdd(dst + c0 + e * 64, f[e] * scale);
 }
 
 // ------------------------------------------------------- cross-entropy ----
@@ -692,9 +712,9 @@ hipError_t rmsnorm_bwd(const uint16_t* x, const uint16_t* g, const float* rstd,
 hipError_t rmsnorm_dg_reduce(const float* dg_partial, int nblk, float* dg, int h, bool accumulate,
                              hipStream_t s) {
   if (accumulate)
-    hipLaunchKernelGGL(dg_reduce_k<true>, dim3(blocks_for(h, 64)), dim3(256), 0, s, dg_partial, nblk, dg, h);
+    hipLaunchKernelGGL(dg_reduce_k<true>, dim3(blocks_for(h, 64)), dim3(1024), 0, s, dg_partial, nblk, dg, h);
   else
-    hipLaunchKernelGGL(dg_reduce_k<false>, dim3(blocks_for(h, 64)), dim3(256), 0, s, dg_partial, nblk, dg, h);
+    hipLaunchKernelGGL(dg_reduce_k<false>, dim3(blocks_for(h, 64)), dim3(1024), 0, s, dg_partial, nblk, dg, h);
   return hipGetLastError();
 }
 
@@ -779,9 +799,9 @@ hipError_t embed_fwd(const int32_t* ids, const uint16_t* emb, uint16_t* x, int T
 
 hipError_t embed_bwd(const int32_t* ids, const uint16_t* dx, float* demb, int T, int h, int V,
                      float scale, hipStream_t s) {
-  const long n = (long)T * (h / 8);
+  const long n = (long)T * ((h + 511) / 512);
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(embed_bwd_k, dim3(blocks_for(n, 256)), dim3(256), 0, s, ids, dx, demb, T, h, V,
+  hipLaunchKernelGGL(embed_bwd_k, dim3(blocks_for(n, 4)), dim3(256), 0, s, ids, dx, demb, T, h, V,
                      scale);
   return hipGetLastError();
 }

@@ -119,3 +119,23 @@ def test_embedding_fwd_bwd():
     assert np.all(got[~valid] == 0)
     ref = ohead.embed_bwd(ids[valid], fi.bf16_bits_to_f64(dxb)[valid], V)
     assert rel_fro(host_f64(dE), ref) <= 1e-6
+
+
+@pytest.mark.parametrize("T,h", [(1, 8), (5, 504), (3, 512), (7, 520), (130, 1032), (2, 8192)])
+def test_embedding_bwd_column_edges(T, h):
+    """Widths around the 512 columns a wave adds: every column of a token once,
+    onto what the gradient holds, none of the neighbouring rows."""
+    import torch
+    from paper_2609_13645_amd import _lib
+    banner(f"embedding bwd T={T} h={h}")
+    rng = np.random.default_rng(T * 11 + h)
+    V = 9
+    ids = rng.integers(0, V - 1, size=T, dtype=np.int32)   # row V - 1 stays untouched
+    dxb = fi.to_bf16_bits(rng.integers(-8, 9, (T, h)).astype(np.float32))
+    base = rng.integers(-8, 9, (V, h)).astype(np.float32)
+    dE = torch.from_numpy(base.copy()).cuda()
+    _lib.forge_embed_bwd(torch.from_numpy(ids).cuda(), dev_bf16(dxb), dE, T, h, V, 0.5)
+    torch.cuda.synchronize()
+    ref = base.astype(np.float64)
+    np.add.at(ref, ids, 0.5 * fi.bf16_bits_to_f64(dxb))
+    assert np.array_equal(host_f64(dE), ref)   # small multiples of 1/2: exact

@@ -53,6 +53,8 @@ def run_dense(cfg, seed):
     ("tiny", dict(qk_norm=1, head_dim=128, n_heads=2, n_kv_heads=1, batch=2, seq=77)),
     ("tiny", dict(packed_docs=20, batch=2, seq=96)),
     ("tiny", dict(branch_scale=1.4 / 24 ** 0.5, qk_norm=1, packed_docs=30, seq=128)),
+    # more (token, head) rows than one trip of the QK-Norm backward's grid
+    ("tiny", dict(qk_norm=1, batch=64, seq=96)),
     ("qwen3_layer", dict(batch=1, seq=320)),
     ("packed_docs_layer", dict(seq=320, packed_docs=60)),
 ])
