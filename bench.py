@@ -267,7 +267,7 @@ def kernel_rooflines(cfg, reps, out=sys.stdout):
     work per launch and the fraction of its roofline: bf16 MFMA peak for the
     products, HBM bandwidth for the elementwise kernels and AdamW. The
     products are the layer's twelve GEMMs with the layouts and epilogues the
-    layer uses; attention backward is the dQ kernel plus the dV and dK passes
+    layer uses; attention backward is the dQ kernel plus the dK / dV pass
     (a kernel trace of this run splits it)."""
     import torch
     from paper_2609_13645_amd import _lib, runtime
@@ -345,7 +345,7 @@ def kernel_rooflines(cfg, reps, out=sys.stdout):
     timed("attention fwd", f"attn_fwd_k<{d}>",
           lambda: _lib.forge_attention_fwd(ac, x_qkv, o, lse, stream), 4.0 * d * pairs, "TFLOP/s")
     timed("attention bwd (counted: 2x fwd)",
-          f"attn_bwd_prep_k<{d}> + attn_bwd_dv_k<{d}> + attn_bwd_dk_k<{d}> + attn_bwd_dq_k<{d}>",
+          f"attn_bwd_prep_k<{d}> + attn_bwd_kv_k<{d}> + attn_bwd_dq_k<{d}>",
           lambda: _lib.forge_attention_bwd(ac, x_qkv, o, lse, x_hq, dqkv, aws, stream),
           8.0 * d * pairs, "TFLOP/s")
 

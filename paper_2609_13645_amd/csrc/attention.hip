@@ -1,8 +1,8 @@
 // Causal grouped-query flash attention on gfx950 MFMA: forward, and the
 // backward as a key-owned kernel that forms S, P, dP and dS once per (key,
-// query) block, accumulates dV of a kv head over every query head of its GQA
-// group and stores dS, then one key-owned and one query-owned product over
-// the stored dS for dK and dQ. The paper's H100 kernel accumulates dQ
+// query) block, accumulates dV and dK of a kv head over every query head of
+// its GQA group and stores dS, then a query-owned product over the stored dS
+// for dQ. The paper's H100 kernel accumulates dQ
 // through a flat global buffer (App. D, "Anatomy of a Forged Kernel"); here
 // no output takes fp32 atomics, so every output is deterministic.
 //
@@ -26,6 +26,7 @@
 // mask is evaluated only on tiles that straddle the diagonal, and waves whose
 // rows are fully masked skip their MFMAs.
 #include <type_traits>
+#include <utility>
 
 #include "common.h"
 #include "kernels.h"
@@ -178,6 +179,16 @@ __device__ __forceinline__ void zero(f32x16_t& a) {
 //  * Inline asm here only reads LDS into registers and waits; it never reads
 //    an MFMA result (the compiler does not insert the wait states an MFMA
 //    result needs before an asm consumer).
+// f(0), f(1), .. f(N - 1) with compile-time indices
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+
 namespace fa {
 
 __device__ __forceinline__ uint32_t lds_off(const void* p) {
@@ -491,37 +502,32 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_k(AttnArgs a, bf16_t* __restr
 }
 
 // ------------------------------------------------------------ backward ----
-// Four launches and five MFMA products in all (S recomputed once), with no
+// Three launches and five MFMA products in all (S formed once), with no
 // atomics, so every output is deterministic:
 //  1. attn_bwd_prep_k: per query, -delta = -rowsum(dO * O) and
 //     -LSE log2(e) (the exponent offset of P = exp(S - LSE) in base 2).
-//  2. attn_bwd_dv_k, key-owned (64 keys of a kv head per block):
-//     S = Q K^T, P, dP = dO V^T, dS = P (dP - delta); dV = sum P^T dO over
-//     the GQA group; dS goes to a scratch buffer in bf16, the precision the
-//     dK and dQ products take it in.
-//  3. attn_bwd_dk_k, key-owned: dK = scale * sum dS^T Q from the stored dS.
-//  4. attn_bwd_dq_k, query-owned: dQ = scale * dS K from the stored dS.
+//  2. attn_bwd_kv_k, key-owned (64 keys of a kv head per block):
+//     S = Q K^T, P, dP = dO V^T, dS = P (dP - delta); dV = sum P^T dO and
+//     dK = scale * sum dS^T Q over the GQA group; dS goes to a scratch buffer
+//     in bf16, the precision the dK and dQ products take it in.
+//  3. attn_bwd_dq_k, query-owned: dQ = scale * dS K from the stored dS.
+// (and attn_bwd_kv_sum_k where 2 splits its blocks' pairs.)
 // The paper's H100 kernel accumulates dQ through fp32 atomics in a flat
-// buffer (App. D); here dQ is a product of its own over the stored dS, and
-// dK no longer needs S and dP formed a second time.
+// buffer (App. D); here dQ is a product of its own over the stored dS.
 //
 // dS layout, per (batch, head): for 64-key tile kt, one 4 KB block per
 // 32-query slab j = 2 kt .. NS - 1 (NS = ceil(seq / 32)) in slab order, so
 // only the causal half is stored. A block holds its 64 x 32 values in the
-// dV pass's accumulator order: value 4 g + e of lane hh * 32 + l32 of key
+// kv pass's accumulator order: value 4 g + e of lane hh * 32 + l32 of key
 // block kb, (key 32 kb + l32, query 8 g + 4 hh + e), is element
 // 4 (g & 1) + e of the 16-byte piece at
 //   kb * 2 KB + u * 1 KB + 512 hh + ((16 l32) ^ (128 hh) ^ (64 u)),  u = g / 2.
-// (The LDS serves a 16-byte read 16 lanes at a time from 64 banks: the dK
-// pass's B-fragment reads take 16 consecutive keys' pieces, a contiguous
-// 256 bytes; the XORs put a key's two lane halves 128 bytes apart and the
-// two query halves 64 bytes apart, so the dQ pass's transposed reads cover
-// all banks too.)
-// Every
-// visited block is written whole (zeros where the mask or the sequence end
-// removes a score). That order is also the dK pass's B-fragment order
-// (loaded straight into registers, 1 KB per wave instruction); the dQ pass
-// reads its transpose with ds_read_b64_tr_b16.
+// (The LDS serves a 16-byte read 16 lanes at a time from 64 banks: the XORs
+// put a key's two lane halves 128 bytes apart and the two query halves 64
+// bytes apart, so the dQ pass's transposed reads cover all banks.)
+// Every visited block is written whole (zeros where the mask or the sequence
+// end removes a score); the dQ pass reads its transpose with
+// ds_read_b64_tr_b16.
 struct DsLayout {
   int ns;      // 32-query slabs of the sequence
   long head;   // elements per (batch, head)
@@ -565,14 +571,15 @@ __global__ __launch_bounds__(256) void attn_bwd_prep_k(const bf16_t* __restrict_
   }
 }
 
-// 2-3. Key-owned blocks: 64 keys [k0, k0 + 64) of one (batch, kv head), four
+// 2. Key-owned blocks: 64 keys [k0, k0 + 64) of one (batch, kv head), four
 // waves, one per SIMD. The block's work is every (query head of the GQA
 // group, 32-query slab at or after k0) pair; wave w takes pairs w, w + 4,
 // ... and accumulates over them for all 64 keys, streaming each pair's
 // operands through a private LDS double buffer (no block barrier in the
 // loop). At the end the four waves' sums are added through LDS in wave
-// order, so the result does not depend on timing, and written as bf16: no
-// partials leave the block, and K / V are read once per GQA group.
+// order, so the result does not depend on timing, and written as bf16 (or,
+// where a block holds one split of the pairs, as fp32 partial sums); K / V
+// are read once per GQA group.
 template <int D>
 struct KvPlan {
   static constexpr int BK = 64, BQ = 32;
@@ -580,14 +587,15 @@ struct KvPlan {
   static constexpr int RED = BK * (D + 4) / 4;    // one wave's [64][D + 4] fp32 sums
   static constexpr int LPR = D / 8, RPI = 64 / LPR, PER = BQ / RPI;  // DMA of a slab
 };
-// dV pass: per-wave buffer (Q, dO slabs, -LSE log2 e | -delta) and its DMA
-// instructions per pair
+// A wave's buffer (Q, dO slabs, -LSE log2 e | -delta) and its DMA instructions
+// per pair; behind the eight buffers, at D = 128, tiles of V and K.
 template <int D>
 struct KvBuf {
   using P = KvPlan<D>;
   static constexpr int WBUF = 2 * P::SLAB + 16;
   static constexpr int DMA = 2 * P::PER + 1;
-  static constexpr int ARR = 4 * WBUF > 2 * P::RED ? 4 * WBUF : 2 * P::RED;
+  static constexpr int ALL = 8 * WBUF + (D == 128 ? 3 * P::SLAB : 0);   // V and half of K at D = 128
+  static constexpr int ARR = ALL > 4 * P::RED ? ALL : 4 * P::RED;
 };
 // Key tile, batch row, kv head and split of a key-owned block: kv head fastest,
 // key tile slowest.
@@ -616,26 +624,27 @@ __device__ __forceinline__ float* kv_part(const AttnArgs& a, float* part, const 
   return part + ((k.z * T + row) * a.n_kv_heads + k.m) * D;
 }
 
-template <int D>
-__device__ __forceinline__ void slab_offsets(long ld, int lane, uint32_t (&off)[KvPlan<D>::PER]) {
-  using P = KvPlan<D>;
-#pragma unroll
-  for (int i = 0; i < P::PER; ++i) {
-    const int row = i * P::RPI + lane / P::LPR;
-    const int c = (lane % P::LPR) ^ fsw<D>(row);
-    off[i] = (uint32_t)(((long)row * ld + c * 8) * 2);
-  }
+// One DMA instruction: 16 bytes per lane from a buffer of `bytes` bytes (zeros
+// past its end), or 4 bytes per lane.
+__device__ __forceinline__ void dma_16(const void* base, int bytes, uint4* lds, uint32_t off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, bytes, 0x00020000),
+      (lds_ptr_t)lds, 16, off, 0, 0, 0);
 }
-// 32 rows [row0, row0 + 32) of a [*, ld] bf16 matrix into a natural tile;
-// rows at or past lim read as zeros.
-template <int D>
-__device__ __forceinline__ void dma_slab(const bf16_t* base, long ld, int row0, int lim,
-                                         uint4* lds, const uint32_t* off) {
-  using P = KvPlan<D>;
-  const __amdgpu_buffer_rsrc_t r = rsrc_n(base + (long)row0 * ld, (long)(lim - row0) * ld * 2);
-#pragma unroll
-  for (int i = 0; i < P::PER; ++i)
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)(lds + i * 64), 16, off[i], 0, 0, 0);
+// What is left of a matrix from a row on: its address and bytes.
+struct Rest {
+  const char* p;
+  int n;
+  __device__ __forceinline__ Rest(const bf16_t* base, long bytes)
+      : p(reinterpret_cast<const char*>(base)),
+        n(bytes <= 0 ? 0 : bytes > 0x7FFFFFF0L ? 0x7FFFFFF0 : (int)bytes) {}
+  __device__ __forceinline__ void skip(int step) {
+    p += step;
+    n = n > step ? n - step : 0;
+  }
+};
+__device__ __forceinline__ void dma_4(const float* base, uint4* lds, uint32_t off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc(base), (lds_ptr_t)lds, 4, off, 0, 0, 0);
 }
 
 // The four waves' [64 keys][D] accumulators (acc[db][kb]: rows d, columns
@@ -692,23 +701,59 @@ __device__ __forceinline__ void kv_reduce_store(const f32x16_t (&acc)[D / 32][2]
   }
 }
 
-// 2. dV pass. Per pair: S and dP (accumulators starting at -delta, so they
-// hold dP - delta), P = exp2(S c - LSE log2 e), dS = P (dP - delta) stored,
-// dV^T += dO^T P. The wave keeps K and V of its 64 keys in registers as two
-// 32-key column blocks, so every Q / dO fragment read from LDS feeds two
-// MFMAs.
+// Per pair: S, P = exp2(S c - LSE log2 e), dP, dS = P (dP + (-delta)) stored,
+// dV^T += dO^T P, dK^T += Q^T dS. The block's K and V rows are held as two 32-key
+// column blocks, so every Q / dO fragment read from LDS feeds two MFMAs. dK comes
+// from the dS just formed: as a pass of its own it read the whole stored dS once
+// more (8.6 GB at 16384 tokens and 32 heads) and was bound by that.
+// One wave per SIMD, 512 registers each. At D = 128 the dV and dK accumulators
+// take half of them; V and the first 32 keys of K then stay in LDS (32-row tiles
+// that all four waves read), 96 registers less: with V alone the compiler
+// reloaded K fragments from scratch between the MFMAs.
+// dV and dK together, alone: 4 x 4096 tokens, 16 / 8 heads of 128, 885 us as two
+// passes (605 + 280, each pair's products and vector work one after the other),
+// 671 here; 16384 tokens, 32 / 8 heads, 6.52 ms and 5.10; 4 x 2047 tokens, 32 / 8
+// heads of 64, 337 us and 240.
 template <int D>
-__global__ __launch_bounds__(256, 1) void attn_bwd_dv_k(AttnArgs a,
+constexpr bool kVInLds = D == 128;
+
+// K and V fragments that step i of a pair takes from LDS.
+template <int D>
+constexpr int kv_extra(int i) {
+  return !kVInLds<D> ? 0 : i < D / 16 ? 1 : i < D / 8 ? 2 : 0;
+}
+// LDS reads issued after those that step i waits for: ahead of step 0 the first
+// w fragments and the K fragments of steps 0 and 1; at the end of step j fragment
+// j + w (two reads where it is transposed), then the K or V of step j + 2.
+template <int D>
+constexpr int kv_behind(int i, int nst, int w) {
+  int n = 0;
+  for (int f = i + 1; f < i + w; ++f)
+    if (f < nst) n += f < D / 8 ? 1 : 2;
+  if (kv_extra<D>(i) == 0) {
+    for (int j = i - w; j < i; ++j)
+      if (j >= 0) n += kv_extra<D>(j + 2);
+    return n;
+  }
+  if (i == 0) return kv_extra<D>(1);
+  const int f = i - 1 + w;
+  return (f < nst ? (f < D / 8 ? 1 : 2) : 0) + kv_extra<D>(i + 1);
+}
+
+template <int D>
+__global__ __launch_bounds__(256, 1) void attn_bwd_kv_k(AttnArgs a,
                                                        const bf16_t* __restrict__ dout,
                                                        const float* __restrict__ delta,
                                                        bf16_t* __restrict__ ds,
-                                                       bf16_t* __restrict__ dv, long ld_d,
-                                                       float* __restrict__ part, int splits) {
+                                                       bf16_t* __restrict__ dv,
+                                                       bf16_t* __restrict__ dk, long ld_d,
+                                                       float* __restrict__ pv,
+                                                       float* __restrict__ pk, int splits) {
   using P = KvPlan<D>;
   using B = KvBuf<D>;
+  constexpr bool VL = kVInLds<D>;
   constexpr int BK = P::BK, BQ = P::BQ, SLAB = P::SLAB, KK = D / 16, DB = D / 32;
-  __shared__ uint4 sm0[B::ARR];
-  __shared__ uint4 sm1[B::ARR];
+  __shared__ __attribute__((aligned(256))) uint4 sm[B::ARR];
 
   const int S = a.seq;
   const int grp = a.n_heads / a.n_kv_heads;
@@ -730,330 +775,325 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dv_k(AttnArgs a,
 
   // K and V rows of the lane's two keys k0 + l32 and k0 + 32 + l32: the
   // B operands of S and dP
-  bf16x8_t kf[2][KK], vf[2][KK];
+  bf16x8_t kf[2][KK], vf[2][VL ? 1 : KK];   // (VL: kf[1] only)
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb) {
     const int key = k0 + kb * 32 + l32;
     const long r = (rb + key) * a.ld_qkv + (long)m * D + hh * 8;
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
-      kf[kb][kk] = gload_frag(a.k + r + kk * 16, key < S);
-      vf[kb][kk] = gload_frag(a.v + r + kk * 16, key < S);
+      if (!VL || kb == 1) kf[kb][kk] = gload_frag(a.k + r + kk * 16, key < S);
+      if constexpr (!VL) vf[kb][kk] = gload_frag(a.v + r + kk * 16, key < S);
     }
   }
-  f32x16_t acc[DB][2];
+  f32x16_t acc[DB][2], acck[DB][2];
 #pragma unroll
   for (int db = 0; db < DB; ++db)
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) zero(acc[db][kb]);
+    for (int kb = 0; kb < 2; ++kb) {
+      zero(acc[db][kb]);
+      zero(acck[db][kb]);
+    }
   const float c = a.scale * kLog2e;
 
-  uint32_t qoff[P::PER], ooff[P::PER];
-  slab_offsets<D>(a.ld_qkv, lane, qoff);
-  slab_offsets<D>(ldo, lane, ooff);
-  uint32_t ro[KK], to[DB][2];
-  frag_offsets<D>(lane, ro, to);
-  const __amdgpu_buffer_rsrc_t drs = rsrc(delta);
+  // Byte offsets, few registers' worth (the swizzle is linear in XOR and every
+  // tile starts at a multiple of a row): instruction i of a slab's DMA takes
+  // rows i RPI .. at chunk c0 ^ fsw(i RPI); fragment kk of a row is at ro ^ 32 kk,
+  // the transposed fragment of column block db at to ^ 64 db.
+  const uint32_t c0 = (uint32_t)(lane % P::LPR ^ fsw<D>(lane / P::LPR)) * 16;
+  const uint32_t qrow = (uint32_t)(lane / P::LPR * a.ld_qkv * 2);
+  const uint32_t orow = (uint32_t)(lane / P::LPR * ldo * 2);
+  uint32_t ros[KK], tos[DB][2];
+  frag_offsets<D>(lane, ros, tos);
+  const uint32_t ro = ros[0], to0 = tos[0][0], to1 = tos[0][1];
+  // V rows of the block's keys, then K rows of the first 32: natural 32-row tiles
+  // behind the waves' buffers
+  uint4* vt = sm + 8 * B::WBUF;
+  if constexpr (VL) {
+    for (int i = wave; i < 3 * P::PER; i += 4) {
+      const int t = i / P::PER, row = (i % P::PER) * P::RPI + lane / P::LPR;
+      const int r0 = k0 + (t == 1 ? 32 : 0);
+      const bf16_t* src = t == 2 ? a.k : a.v;
+      const Rest left(src + (rb + r0) * a.ld_qkv + (long)m * D, (long)(S - r0) * a.ld_qkv * 2);
+      dma_16(left.p, left.n, vt + i * 64,
+             (uint32_t)(((long)row * a.ld_qkv + ((lane % P::LPR) ^ fsw<D>(row)) * 8) * 2));
+    }
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    __syncthreads();
+  }
   // the lane's dS piece (elements) in a 1 KB half; half u adds the XOR u * 32
   const int pc0 = 256 * hh + ((8 * l32) ^ (64 * hh));
 
-  // pair p: query head m * grp + p % grp, slab j0 + ns - 1 - p / grp. Every
+  // Pair p: query head m * grp + p % grp, slab j0 + ns - 1 - p / grp. Every
   // block of the kv group walks the slabs from the sequence end, head-minor,
   // so the blocks running at once read the same Q / dO slabs (one XCD's L2
   // serves them; block ids cycle through the kv heads, which the dispatcher
-  // spreads over the XCDs)
-  auto load = [&](int p, uint4* base) __attribute__((always_inline)) {
-    const int n = m * grp + p % grp;
-    const int q0 = (j0 + ns - 1 - p / grp) * BQ;
-    dma_slab<D>(a.q + rb * a.ld_qkv + (long)n * D, a.ld_qkv, q0, S, base, qoff);
-    dma_slab<D>(dout + rb * ldo + (long)n * D, ldo, q0, S, base + SLAB, ooff);
-    // lanes 0-31: -LSE log2(e) of the slab's queries; lanes 32-63: -delta
-    const long li = ((long)b * a.n_heads + n) * S + q0 + l32;
-    const uint32_t off = q0 + l32 < S ? (uint32_t)(((hh ? 0 : nrows) + li) * 4) : kOOB;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(drs, (lds_ptr_t)(base + 2 * SLAB), 4, off, 0, 0, 0);
+  // spreads over the XCDs).
+  struct Pair {
+    int n, q0;
+  };
+  // (walked without a division: head and slab advance by the step's)
+  const int p0 = wave + 4 * kb_.z, step = 4 * splits;
+  const int step_n = step % grp, step_q = step / grp * BQ;
+  auto pair_at = [&](int p) __attribute__((always_inline)) {
+    return Pair{m * grp + p % grp, (j0 + ns - 1 - p / grp) * BQ};
+  };
+  auto advance = [&](Pair w) __attribute__((always_inline)) {
+    w.n += step_n;
+    w.q0 -= step_q;
+    if (w.n >= (m + 1) * grp) {
+      w.n -= grp;
+      w.q0 -= BQ;
+    }
+    return w;
+  };
+  // DMA instruction I of a pair into a buffer: the Q slab, the dO slab, then
+  // (lanes 0-31) -LSE log2(e) and (lanes 32-63) -delta of the slab's queries
+  struct Slabs {
+    Rest q, o;
+  };
+  const int qstep = P::RPI * (int)a.ld_qkv * 2, ostep = P::RPI * (int)ldo * 2;
+  auto slabs = [&](const Pair& w) __attribute__((always_inline)) {
+    return Slabs{Rest(a.q + (rb + w.q0) * a.ld_qkv + (long)w.n * D, (long)(S - w.q0) * a.ld_qkv * 2),
+                 Rest(dout + (rb + w.q0) * ldo + (long)w.n * D, (long)(S - w.q0) * ldo * 2)};
+  };
+  auto dma = [&](auto I, const Pair& w, Slabs& sl, uint4* base) __attribute__((always_inline)) {
+    constexpr int i = I;
+    if constexpr (i < P::PER) {
+      dma_16(sl.q.p, sl.q.n, base + i * 64, qrow + (c0 ^ fsw<D>(i * P::RPI) * 16));
+      sl.q.skip(qstep);
+    } else if constexpr (i < 2 * P::PER) {
+      constexpr int j = i - P::PER;
+      dma_16(sl.o.p, sl.o.n, base + SLAB + j * 64, orow + (c0 ^ fsw<D>(j * P::RPI) * 16));
+      sl.o.skip(ostep);
+    } else {
+      const long li = ((long)b * a.n_heads + w.n) * S + w.q0 + l32;
+      dma_4(delta, base + 2 * SLAB,
+            w.q0 + l32 < S ? (uint32_t)(((hh ? 0 : nrows) + li) * 4) : kOOB);
+    }
   };
 
-  auto pair = [&](const uint4* base, int p) __attribute__((always_inline)) {
-    // this buffer's DMA has landed once only the other buffer's (issued
-    // after it) can still be in flight
+  // One pair as a single stream of 2 (2 KK + 4 DB) MFMAs: the KK steps of S,
+  // the KK of dP, then the 2 DB of dV and the 2 DB of dK (16 queries, one
+  // 32-column block each);
+  // a step is one fragment from LDS feeding both key blocks. One wave per
+  // SIMD: nothing else hides this wave's vector work, so every MFMA is
+  // followed by about its own duration of it (32 cycles, eight plain or two
+  // transcendental operations), issued while the matrix unit runs:
+  //   S     the previous pair's dS to memory, then the next pair's DMA (into
+  //         the other buffer, free since the previous pair ended)
+  //   dP    the probabilities of the first 16 queries (and, at D = 128, four
+  //         scores of the rest), from the third MFMA on, when S is complete
+  //   dV 1  the remaining probabilities
+  //   dV 2  dS = P (dP - delta), packed; the second 16 queries' under the
+  //         first half of dK
+  // Fragments are read W steps ahead (inline asm with counted waits). As three
+  // separate phases (products, then all probabilities and dS, then dV) the
+  // matrix unit stood still during the second.
+  constexpr int NST = 2 * KK + 4 * DB, W = 4;
+  constexpr int EP = D == 128 ? 20 : 16;   // probabilities formed under dP
+  u32x4_t dsp[4];              // packed dS of the last pair (piece u of key block kb: 2 kb + u)
+  bf16_t* dsblk = nullptr;     // its block
+  // dS is written in accumulator order: 16-byte stores, 1 KB per wave
+  // instruction; nontemporal, since it is read back only after the pass (as
+  // ordinary stores, the dirty lines the memory-side cache holds at the end
+  // are written back while the next pass reads dS: 7 % on that pass)
+  auto store_ds = [&]() __attribute__((always_inline)) {
+    static_for<4>([&](auto J) __attribute__((always_inline)) {
+      constexpr int j = J;
+      __builtin_nontemporal_store(
+          dsp[j], reinterpret_cast<u32x4_t*>(dsblk + (j / 2) * 1024 + (j % 2) * 512 +
+                                             (pc0 ^ ((j % 2) * 32))));
+    });
+  };
+  auto pair = [&](const uint4* base, const Pair& w, uint4* next, const Pair& wn)
+      __attribute__((always_inline)) {
+    // this buffer's DMA (and the dS stores issued before it) have landed
     __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(B::DMA));
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     __builtin_amdgcn_sched_barrier(0);
-    const int n = m * grp + p % grp;
-    const int q0 = (j0 + ns - 1 - p / grp) * BQ;
-    const float* Lp = reinterpret_cast<const float*>(base + 2 * SLAB);
-    const float* Dl = Lp + BQ;
+    const int q0 = w.q0;
+    Slabs sl = slabs(wn);
+    // (opaque, so that the sums with it stay at the reads: hoisted out of the
+    // loop for both buffers they take 32 registers that the kernel lacks)
+    uint32_t ab = fa::lds_off(base);
+    asm volatile("" : "+v"(ab));
+    // -LSE log2(e), later -delta, of the lane's queries 8 g + 4 hh + {0..3}
+    bf16x8_t row[4];
+    constexpr int LO = 2 * SLAB * 16;
+    const uint32_t lb = ab + hh * 16;
+    static_for<4>([&](auto G) __attribute__((always_inline)) {
+      row[G] = fa::rd_b128<LO + G * 32>(lb);
+    });
+    uint32_t vb = fa::lds_off(vt) + ro;
+    const uint32_t ra = ab + ro, ta0 = ab + to0, ta1 = ab + to1;
+    bf16x8_t fr[W], vr[2][2];
+    auto read = [&](auto I) __attribute__((always_inline)) {
+      constexpr int i = I, T0 = SLAB * 16;   // the dO slab
+      if constexpr (i < KK) {
+        fr[i % W] = fa::rd_b128<0>(ra ^ (i * 32));
+      } else if constexpr (i < 2 * KK) {
+        fr[i % W] = fa::rd_b128<T0>(ra ^ ((i - KK) * 32));
+      } else {
+        // dO rows 0.., 16.. for dV, then those of Q for dK
+        constexpr int db = (i - 2 * KK) % DB, g = (i - 2 * KK) / DB;
+        constexpr int T = (g < 2 ? T0 : 0) + (g % 2) * 16 * D * 2;
+        fr[i % W] = fa::rd_tr<T>(ta0 ^ (db * 64), ta1 ^ (db * 64));
+      }
+    };
+    // the K (first key block) or V (both) fragments of step I
+    auto read_kv = [&](auto I) __attribute__((always_inline)) {
+      constexpr int i = I, k = i % KK;
+      if constexpr (i < KK) {
+        vr[i % 2][0] = fa::rd_b128<2 * SLAB * 16>(vb ^ (k * 32));
+      } else {
+        vr[i % 2][0] = fa::rd_b128<0>(vb ^ (k * 32));
+        vr[i % 2][1] = fa::rd_b128<SLAB * 16>(vb ^ (k * 32));
+      }
+    };
     f32x16_t sc[2], dp[2];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const float4 dd = *reinterpret_cast<const float4*>(Dl + g * 8 + hh * 4);
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-        dp[kb][g * 4 + 0] = dd.x;
-        dp[kb][g * 4 + 1] = dd.y;
-        dp[kb][g * 4 + 2] = dd.z;
-        dp[kb][g * 4 + 3] = dd.w;
-      }
-    }
-    // S and dP: each row fragment feeds both key blocks. The fragments of
-    // a product are all read at once (inline asm: the compiler would wait
-    // for each read before its MFMAs) and each MFMA pair waits only for its
-    // own fragment.
-    const uint32_t ab = fa::lds_off(base);
-    auto rows_product = [&](auto OFF, const bf16x8_t (&bk)[2][KK], f32x16_t (&cc)[2], bool from0)
-        __attribute__((always_inline)) {
-      constexpr int O = decltype(OFF)::value;
-      bf16x8_t f[KK];
-#pragma unroll
-      for (int kk = 0; kk < KK; ++kk) f[kk] = fa::rd_b128<O>(ab + ro[kk]);
-#pragma unroll
-      for (int kk = 0; kk < KK; ++kk) {
-        switch (KK - 1 - kk) {
-          case 7: fa::wait_lds<7>(); break;
-          case 6: fa::wait_lds<6>(); break;
-          case 5: fa::wait_lds<5>(); break;
-          case 4: fa::wait_lds<4>(); break;
-          case 3: fa::wait_lds<3>(); break;
-          case 2: fa::wait_lds<2>(); break;
-          case 1: fa::wait_lds<1>(); break;
-          default: fa::wait_lds<0>(); break;
+    bf16x8_t pf[2];      // P of 16 queries packed, per key block
+    // probability of score x (of 32): the first 16 queries of both key blocks,
+    // then the others
+    auto prob = [&](auto X) __attribute__((always_inline)) {
+      constexpr int kb = (X % 16) / 8, i = (X / 16) * 8 + X % 8;
+      const f32x4_t lv = __builtin_bit_cast(f32x4_t, row[i >> 2]);
+      sc[kb][i] = fast_exp2(__builtin_fmaf(sc[kb][i], c, lv[i & 3]));
+    };
+    // four values of dS (half of a piece): the first 16 queries of both key
+    // blocks, then the others
+    auto dscore = [&](auto H) __attribute__((always_inline)) {
+      constexpr int kb = (H / 2) % 2, u = H / 4, i = u * 8 + (H % 2) * 4;
+      const f32x4_t nd = __builtin_bit_cast(f32x4_t, row[i >> 2]);
+      float v[4];
+      static_for<4>([&](auto E) __attribute__((always_inline)) {
+        constexpr int e = E;
+        v[e] = sc[kb][i + e] * (dp[kb][i + e] + nd[e]);
+      });
+      const uint32_t w0 = pack2(v[0], v[1]), w1 = pack2(v[2], v[3]);
+      dsp[2 * kb + u][(H % 2) * 2] = w0;
+      dsp[2 * kb + u][(H % 2) * 2 + 1] = w1;
+    };
+    // the vector work behind MFMA x
+    auto under = [&](auto X) __attribute__((always_inline)) {
+      constexpr int x = X;
+      if constexpr (x < 2 * KK) {
+        if constexpr (x == 0) {
+          if (dsblk) store_ds();
         }
-        fa::bind(f[kk]);
-        cc[0] = MFMA(f[kk], bk[0][kk], (kk == 0 && from0) ? f32x16_t{} : cc[0]);
-        cc[1] = MFMA(f[kk], bk[1][kk], (kk == 0 && from0) ? f32x16_t{} : cc[1]);
-        __builtin_amdgcn_sched_barrier(0);   // keep each pair at its own wait
+        constexpr int i0 = B::DMA * x / (2 * KK), i1 = B::DMA * (x + 1) / (2 * KK);
+        static_for<i1 - i0>([&](auto V) __attribute__((always_inline)) {
+          dma(fa::ic<i0 + V>{}, wn, sl, next);
+        });
+      } else if constexpr (x < 4 * KK) {
+        constexpr int N = 2 * KK - 2, t = x - 2 * KK - 2;
+        if constexpr (t >= 0) {
+          constexpr int v0 = EP * t / N, v1 = EP * (t + 1) / N;
+          static_for<v1 - v0>([&](auto V) __attribute__((always_inline)) { prob(fa::ic<v0 + V>{}); });
+        }
+        if constexpr (t == N - 1) {
+          pf[0] = pack_frag(sc[0], 0);
+          pf[1] = pack_frag(sc[1], 0);
+        }
+      } else if constexpr (x < 4 * KK + 2 * DB) {
+        constexpr int N = 2 * DB, R = 32 - EP, t = x - 4 * KK;
+        constexpr int v0 = EP + R * t / N, v1 = EP + R * (t + 1) / N;
+        static_for<v1 - v0>([&](auto V) __attribute__((always_inline)) { prob(fa::ic<v0 + V>{}); });
+        if constexpr (t == N - 1) {
+          pf[0] = pack_frag(sc[0], 1);
+          pf[1] = pack_frag(sc[1], 1);
+        }
+      } else if constexpr (x < 4 * KK + 6 * DB) {
+        constexpr int N = 4 * DB, t = x - 4 * KK - 2 * DB;
+        constexpr int h0 = 8 * t / N, h1 = 8 * (t + 1) / N;
+        static_for<h1 - h0>([&](auto V) __attribute__((always_inline)) { dscore(fa::ic<h0 + V>{}); });
       }
     };
-    rows_product(fa::ic<0>{}, kf, sc, true);
-    rows_product(fa::ic<SLAB * 16>{}, vf, dp, false);
-    // causal mask and sequence tail (diagonal and last slabs only): -inf
-    // scores, so exp2 gives 0
-    if (q0 < k0 + BK - 1 || q0 + BQ > S) {
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int q = q0 + (i >> 2) * 8 + hh * 4 + (i & 3);
-          if (k0 + kb * 32 + l32 > q || q >= S) sc[kb][i] = -INFINITY;
-        }
+    static_for<W>([&](auto I) __attribute__((always_inline)) { read(I); });
+    if constexpr (VL) {
+      read_kv(fa::ic<0>{});
+      read_kv(fa::ic<1>{});
     }
-    // P into sc, dS into dp
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const float4 ll = *reinterpret_cast<const float4*>(Lp + g * 8 + hh * 4);
-      const float lv[4] = {ll.x, ll.y, ll.z, ll.w};
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int i = g * 4 + e;
-          const float pr = fast_exp2(__builtin_fmaf(sc[kb][i], c, lv[e]));
-          dp[kb][i] = pr * dp[kb][i];
-          sc[kb][i] = pr;
-        }
-    }
-    // the pair's dS block, in accumulator order: 16-byte stores, 1 KB per
-    // wave instruction; nontemporal, since the block is read back only after
-    // the pass (as ordinary stores, the dirty lines the memory-side cache
-    // holds at the end are written back while the dK pass reads dS: dK
-    // +7 %)
-    bf16_t* blk = ds + ((long)b * a.n_heads + n) * L.head + L.block(kt, q0 / BQ);
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-        __builtin_nontemporal_store(
-            __builtin_bit_cast(u32x4_t, pack_frag(dp[kb], u)),
-            reinterpret_cast<u32x4_t*>(blk + kb * 1024 + u * 512 + (pc0 ^ (u * 32))));
-    // dV^T += dO^T P, 16 queries at a time; each transposed fragment feeds
-    // both key blocks
-    auto quarter = [&](auto SS) __attribute__((always_inline)) {
-      constexpr int ss = decltype(SS)::value;
-      constexpr int T0 = SLAB * 16 + ss * 16 * D * 2;   // dO rows 16 ss ..
-      // all transposed fragments of the quarter in flight (inline asm), each
-      // MFMA pair waiting only for its own two reads
-      bf16x8_t ft[DB];
-#pragma unroll
-      for (int db = 0; db < DB; ++db) ft[db] = fa::rd_tr<T0>(ab + to[db][0], ab + to[db][1]);
-      const bf16x8_t p0 = pack_frag(sc[0], ss), p1 = pack_frag(sc[1], ss);
-#pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        switch (DB - 1 - db) {
-          case 3: fa::wait_lds<6>(); break;
-          case 2: fa::wait_lds<4>(); break;
-          case 1: fa::wait_lds<2>(); break;
-          default: fa::wait_lds<0>(); break;
-        }
-        fa::bind(ft[db]);
-        acc[db][0] = MFMA(ft[db], p0, acc[db][0]);
-        acc[db][1] = MFMA(ft[db], p1, acc[db][1]);
-        __builtin_amdgcn_sched_barrier(0);
+    static_for<NST>([&](auto I) __attribute__((always_inline)) {
+      constexpr int i = I;
+      // (at the first step of the last phases every read has to have returned,
+      // the -delta rows just issued among them)
+      fa::wait_lds<i == 2 * KK + DB ? 0 : kv_behind<D>(i, NST, W)>();
+      fa::bind(fr[i % W]);
+      if constexpr (kv_extra<D>(i) > 0) fa::bind(vr[i % 2][0]);
+      if constexpr (kv_extra<D>(i) > 1) fa::bind(vr[i % 2][1]);
+      if constexpr (i == 0 || i == 2 * KK + DB) {
+        static_for<4>([&](auto G) __attribute__((always_inline)) {
+          fa::bind(row[G]);
+        });
       }
-    };
-    quarter(std::integral_constant<int, 0>());
-    quarter(std::integral_constant<int, 1>());
-  };
-
-  // the wave's pairs through its two buffers (two arrays, so the compiler
-  // waits only for the DMA of the buffer being read)
-  // Every step issues the same DMA count (past the last pair it reloads the
-  // last pair, which is not used), so the wait before reading a buffer can
-  // leave the other buffer's DMA in flight.
-  uint4* my0 = sm0 + wave * B::WBUF;
-  uint4* my1 = sm1 + wave * B::WBUF;
-  const int p0 = wave + 4 * kb_.z, step = 4 * splits;
-  load(min(p0, total - 1), my0);
-  for (int p = p0; p < total; p += 2 * step) {
-    load(min(p + step, total - 1), my1);
-    pair(my0, p);
-    if (p + step >= total) break;
-    load(min(p + 2 * step, total - 1), my0);
-    pair(my1, p + step);
-  }
-  kv_reduce_store<D>(acc, sm0, sm1, wave, lane, 1.0f, dv + (rb + k0) * ld_d + (long)m * D, ld_d,
-                     kv_part<D>(a, part, kb_, rb + k0), (long)a.n_kv_heads * D, S - k0);
-}
-
-// 3. dK pass: dK^T += Q^T dS over the block's pairs. Each pair's Q slab and
-// dS block go through the wave's LDS ring by DMA; the A operand is the Q
-// slab's transposed fragments (as the dV pass reads dO^T), and the dS block
-// is already in B-fragment order, so each B fragment is one 16-byte read
-// (1 KB per wave instruction, contiguous). Each wave keeps KR pairs in
-// flight: the pass streams dS from HBM with little arithmetic per byte.
-template <int D>
-struct DkPlan {
-  using P = KvPlan<D>;
-  static constexpr int KR = 3;                      // ring depth (pairs per wave)
-  static constexpr int SLOT = P::SLAB + 256;        // Q slab + 4 KB dS block
-  static constexpr int MEM = P::PER + 4;            // DMA instructions per pair
-  static constexpr int RING = 4 * KR * SLOT;        // chunks of the four waves' rings
-  static constexpr int ARR = RING > 4 * P::RED ? RING : 4 * P::RED;
-};
-
-template <int D>
-__global__ __launch_bounds__(256, 1) void attn_bwd_dk_k(AttnArgs a, const bf16_t* __restrict__ ds,
-                                                       bf16_t* __restrict__ dk, long ld_d,
-                                                       float* __restrict__ part, int splits) {
-  using P = KvPlan<D>;
-  using R = DkPlan<D>;
-  constexpr int BK = P::BK, BQ = P::BQ, KK = D / 16, DB = D / 32, KR = R::KR;
-  constexpr int NR = 2 * DB + 2;   // LDS reads of one 16-query step
-  __shared__ uint4 sm[R::ARR];
-
-  const int S = a.seq;
-  const int grp = a.n_heads / a.n_kv_heads;
-  const KvBlock kb_(a, splits);
-  const int kt = kb_.kt, m = kb_.m, b = kb_.b;
-  const int k0 = kt * BK;
-  const int j0 = k0 / BQ;
-  const int ns = (S + BQ - 1) / BQ - j0;
-  const int total = grp * ns;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const long rb = (long)b * S;
-  const DsLayout L(S);
-
-  f32x16_t acc[DB][2];
-#pragma unroll
-  for (int db = 0; db < DB; ++db)
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) zero(acc[db][kb]);
-
-  uint32_t qoff[P::PER];
-  slab_offsets<D>(a.ld_qkv, lane, qoff);
-  uint32_t ro[KK], to[DB][2];
-  frag_offsets<D>(lane, ro, to);
-  // the (batch, key tile kt) dS blocks of query head n are consecutive:
-  // pair p's block is ns - 1 - p / grp blocks after the tile's first
-  const bf16_t* dsk = ds + L.tile(kt);
-  uint4* ring = sm + wave * KR * R::SLOT;
-  const uint32_t lb = lane * 16;   // the lane's 16 bytes of each 1 KB of a dS block (DMA)
-  // the lane's B fragments in a dS block: half ss at ss * 1 KB + (pc ^ ss * 64)
-  const uint32_t pc = (uint32_t)(512 * (lane >> 5) + ((16 * (lane & 31)) ^ (128 * (lane >> 5))));
-
-  // pair p into ring slot u: the Q slab, then the dS block (four 1 KB DMA)
-  auto load = [&](int p, int u) __attribute__((always_inline)) {
-    const int n = m * grp + p % grp;
-    const int q0 = (j0 + ns - 1 - p / grp) * BQ;
-    uint4* slot = ring + u * R::SLOT;
-    dma_slab<D>(a.q + rb * a.ld_qkv + (long)n * D, a.ld_qkv, q0, S, slot, qoff);
-    const __amdgpu_buffer_rsrc_t r =
-        rsrc(dsk + ((long)b * a.n_heads + n) * L.head + 2048L * (ns - 1 - p / grp));
-    // (cache policy 2 = non-temporal: each dS block is read once by this
-    // pass, so it need not displace the Q slabs every block re-reads from L2)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)(slot + P::SLAB + i * 64), 16,
-                                               lb + i * 1024, 0, 0, 2);
-  };
-
-  auto pair = [&](int u) __attribute__((always_inline)) {
-    // this pair's DMA has landed once only the KR - 1 pairs issued after it
-    // can still be in flight
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm((KR - 1) * R::MEM));
-    __builtin_amdgcn_sched_barrier(0);
-    const uint32_t ab = fa::lds_off(ring + u * R::SLOT);
-    // both 16-query steps' fragments in flight; each step's MFMAs wait for
-    // its own reads.
-    bf16x8_t ft[2][DB], fb[2][2];
-#pragma unroll
-    for (int db = 0; db < DB; ++db) ft[0][db] = fa::rd_tr<0>(ab + to[db][0], ab + to[db][1]);
-    fb[0][0] = fa::rd_b128<P::SLAB * 16>(ab + pc);
-    fb[0][1] = fa::rd_b128<P::SLAB * 16 + 2048>(ab + pc);
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-      ft[1][db] = fa::rd_tr<16 * D * 2>(ab + to[db][0], ab + to[db][1]);
-    fb[1][0] = fa::rd_b128<P::SLAB * 16 + 1024>(ab + (pc ^ 64));
-    fb[1][1] = fa::rd_b128<P::SLAB * 16 + 2048 + 1024>(ab + (pc ^ 64));
-    fa::wait_lds<NR>();
-    fa::bind(fb[0][0]);
-    fa::bind(fb[0][1]);
-#pragma unroll
-    for (int db = 0; db < DB; ++db) fa::bind(ft[0][db]);
-#pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      acc[db][0] = MFMA(ft[0][db], fb[0][0], acc[db][0]);
-      acc[db][1] = MFMA(ft[0][db], fb[0][1], acc[db][1]);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    fa::wait_lds<0>();
-    fa::bind(fb[1][0]);
-    fa::bind(fb[1][1]);
-#pragma unroll
-    for (int db = 0; db < DB; ++db) fa::bind(ft[1][db]);
-#pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      acc[db][0] = MFMA(ft[1][db], fb[1][0], acc[db][0]);
-      acc[db][1] = MFMA(ft[1][db], fb[1][1], acc[db][1]);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  };
-
-  // The wave's pairs p = p0 + step i; pair i sits in slot i % KR. Every step
-  // issues the same number of DMA instructions (past the last pair it
-  // reloads the last pair, unused), so the wait count above is exact.
-  const int p0 = wave + 4 * kb_.z, step = 4 * splits;
-#pragma unroll
-  for (int u = 0; u < KR - 1; ++u) load(min(p0 + step * u, total - 1), u);
-  bool done = false;
-  for (int p = p0; !done; p += step * KR) {
-#pragma unroll
-    for (int u = 0; u < KR; ++u) {
-      if (!done) {
-        const int pp = p + step * u;
-        if (pp >= total) {
-          done = true;
+      static_for<2>([&](auto KB) __attribute__((always_inline)) {
+        constexpr int kb = KB;
+        if constexpr (i < KK) {
+          if constexpr (VL && kb == 0)
+            sc[kb] = MFMA(fr[i % W], vr[i % 2][0], i == 0 ? f32x16_t{} : sc[kb]);
+          else
+            sc[kb] = MFMA(fr[i % W], kf[kb][i], i == 0 ? f32x16_t{} : sc[kb]);
+        } else if constexpr (i < 2 * KK) {
+          if constexpr (VL)
+            dp[kb] = MFMA(fr[i % W], vr[i % 2][kb], i == KK ? f32x16_t{} : dp[kb]);
+          else
+            dp[kb] = MFMA(fr[i % W], vf[kb][i - KK], i == KK ? f32x16_t{} : dp[kb]);
         } else {
-          load(min(pp + step * (KR - 1), total - 1), (u + KR - 1) % KR);
-          pair(u);
+          constexpr int db = (i - 2 * KK) % DB, g = (i - 2 * KK) / DB;
+          if constexpr (g < 2)
+            acc[db][kb] = MFMA(fr[i % W], pf[kb], acc[db][kb]);
+          else
+            acck[db][kb] = MFMA(fr[i % W], __builtin_bit_cast(bf16x8_t, dsp[2 * kb + g - 2]),
+                                acck[db][kb]);
         }
-      }
-    }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (kb == 1 && i + W < NST) read(fa::ic<i + W>{});
+        if constexpr (VL && kb == 1 && i + 2 < 2 * KK) read_kv(fa::ic<i + 2>{});
+        // causal mask and sequence tail (diagonal and last slabs only), once S
+        // is complete: -inf scores, so exp2 gives 0
+        if constexpr (i == KK && kb == 0) {
+          if (q0 < k0 + BK - 1 || q0 + BQ > S) {
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+              for (int e = 0; e < 16; ++e) {
+                const int q = q0 + (e >> 2) * 8 + hh * 4 + (e & 3);
+                if (k0 + mb * 32 + l32 > q || q >= S) sc[mb][e] = -INFINITY;
+              }
+          }
+        }
+        under(fa::ic<2 * i + kb>{});
+        // the probabilities are done with the LSE rows: -delta takes their place
+        if constexpr (i == 2 * KK + DB - 1 && kb == 1)
+          static_for<4>([&](auto G) __attribute__((always_inline)) {
+            row[G] = fa::rd_b128<LO + BQ * 4 + G * 32>(lb);
+          });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    });
+  };
+
+  // The wave's pairs, alternating between its two buffers (the last pair's
+  // DMA reloads it, unused).
+  uint4* mine = sm + wave * 2 * B::WBUF;
+  int cur = 0;
+  Pair w = pair_at(min(p0, total - 1));
+  Slabs first = slabs(w);
+  static_for<B::DMA>([&](auto I) __attribute__((always_inline)) { dma(I, w, first, mine); });
+  for (int p = p0; p < total; p += step) {
+    const Pair wn = p + step < total ? advance(w) : w;
+    pair(mine + cur * B::WBUF, w, mine + (cur ^ 1) * B::WBUF, wn);
+    dsblk = ds + ((long)b * a.n_heads + w.n) * L.head + L.block(kt, w.q0 / BQ);
+    w = wn;
+    cur ^= 1;
   }
-  kv_reduce_store<D>(acc, sm, sm + 2 * P::RED, wave, lane, a.scale,
+  if (dsblk) store_ds();
+  kv_reduce_store<D>(acc, sm, sm + 2 * P::RED, wave, lane, 1.0f, dv + (rb + k0) * ld_d + (long)m * D,
+                     ld_d, kv_part<D>(a, pv, kb_, rb + k0), (long)a.n_kv_heads * D, S - k0);
+  kv_reduce_store<D>(acck, sm, sm + 2 * P::RED, wave, lane, a.scale,
                      dk + (rb + k0) * ld_d + (long)m * D, ld_d,
-                     kv_part<D>(a, part, kb_, rb + k0), (long)a.n_kv_heads * D, S - k0);
+                     kv_part<D>(a, pk, kb_, rb + k0), (long)a.n_kv_heads * D, S - k0);
 }
 
 // dK and dV from the splits' partial sums, added in split order; eight columns
@@ -1299,8 +1339,8 @@ hipError_t attn_bwd_d(const AttnArgs& a, const uint16_t* o, const uint16_t* dout
   const dim3 qgrid((unsigned)((a.seq + 255) / 256 * a.n_heads * a.batch));
   hipLaunchKernelGGL(attn_bwd_prep_k<D>, pgrid, block, 0, s, o, dout, lse, delta, rows, a.n_heads,
                      a.seq);
-  hipLaunchKernelGGL(attn_bwd_dv_k<D>, kgrid, block, 0, s, a, dout, delta, ds, dv, ld_d, pv, z);
-  hipLaunchKernelGGL(attn_bwd_dk_k<D>, kgrid, block, 0, s, a, ds, dk, ld_d, pk, z);
+  hipLaunchKernelGGL(attn_bwd_kv_k<D>, kgrid, block, 0, s, a, dout, delta, ds, dv, dk, ld_d, pv, pk,
+                     z);
   if (z > 1) {
     const dim3 sgrid((unsigned)((T * (width / 8) + 255) / 256), 2);
     hipLaunchKernelGGL(attn_bwd_kv_sum_k, sgrid, block, 0, s, pk, pv, z, T, width, a.scale, dk, dv,

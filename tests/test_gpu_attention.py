@@ -24,6 +24,10 @@ CASES = [
     # pairs (16 ways, a ragged tail; blocks whose splits have no pair)
     (1, 1000, 16, 1, 128),
     (2, 520, 8, 2, 64),
+    # last key tile of one key, and without a second 32-key block; odd group
+    (1, 65, 4, 2, 128),
+    (2, 95, 6, 2, 128),
+    (1, 289, 9, 3, 64),
 ]
 
 
