@@ -483,8 +483,9 @@ typedef struct {
  * stream of the library's own, so the memory-bound updates of the FFN (or
  * expert and router) weights run while the compute-bound attention backward
  * is in flight (layers of fewer than 2^20 token x hidden elements, where
- * the stream hand-offs would cost more than they save, run the updates in
- * order on `stream`).
+ * the stream hand-offs would cost more than they save, and of 2^26 and more,
+ * whose products fill the chip by themselves, run the updates in order on
+ * `stream`).
  * opt: each used entry's param must be the same pointer as the matching
  *   member of w (the update overwrites the weight in place, after the
  *   backward's last read of it); master, m, v are updated in place.

@@ -443,7 +443,7 @@ forge_status attn_block_fwd(const forge_layer_cfg& c, const Dims& d,
 }
 
 // ---- side streams of the layer backward ----------------------------------------
-// The dense layer backward (from 2^20 token x hidden elements up) runs its
+// The dense layer backward (from 2^20 to 2^26 token x hidden elements) runs its
 // four weight-gradient GEMMs on a second stream of the same device, forked from the caller's stream after each one's
 // inputs exist and joined back before the call's work ends, so they fill the
 // tail waves of the data-gradient GEMMs and the bandwidth-bound kernels in
@@ -467,8 +467,17 @@ struct SideLane {
 SideLane g_side[kMaxDevices];
 std::mutex g_side_init;
 
-// side streams only for layers whose products outlast the event hand-offs
-bool use_side_streams(const Dims& d) { return d.T * d.h >= (1L << 20); }
+// Side streams only for layers whose products outlast the event hand-offs (2048
+// tokens x 2048: 943 us with them, 1005 without) and up to 2^26 token x hidden
+// elements. From there on every product fills the chip for many rounds, so
+// nothing is left to fill, and products sharing it only take each other's cache:
+// dense, 4 x 4096 tokens x 4096, 21.8 ms with them and 21.1 without (with AdamW
+// 22.8 and 22.1; one 16384-token sequence 28.2 and 27.5); 64 experts, 8 x 4096 x
+// 2048, 21.2 and 20.9. At half that size either way: 8192 x 4096, 10.63 and 10.50
+// ms, with AdamW 11.57 and 11.65; 16384 x 2048, 6.21 and 6.20.
+bool use_side_streams(const Dims& d) {
+  return d.T * d.h >= (1L << 20) && d.T * d.h < (1L << 26);
+}
 
 hipError_t side_lane(SideLane** out) {
   int dev = 0;
@@ -1077,8 +1086,7 @@ forge_status layer_bwd(const forge_layer_cfg* cfg, const forge_layer_weights* w,
     uint16_t* dgu = at<uint16_t>(workspace, wk.dgu);
     // weight gradients on the side stream (see SideLane): dW_down as soon
     // as the call starts, dW_gate_up once dgu exists
-    // small layers stay on the caller's stream: there the event hand-offs
-    // cost more than the overlap gains
+    // (use_side_streams: small and very large layers stay on the caller's stream)
     SideLane* side = nullptr;
     if (use_side_streams(d)) FORGE_HIP(side_lane(&side));
     std::unique_lock<std::mutex> lk;

@@ -348,8 +348,9 @@ def uses_side_streams(cfg: dict) -> bool:
     """Whether libforge runs a layer's weight gradients and updates on its
     own streams: from 2^20 token x hidden elements (below, the event
     hand-offs cost more than the overlap gains, and one AdamW launch over
-    all parameters beats one per weight)."""
-    return cfg["batch"] * cfg["seq"] * cfg["hidden"] >= (1 << 20)
+    all parameters beats one per weight) to 2^26 (from there on every product
+    fills the chip by itself)."""
+    return (1 << 20) <= cfg["batch"] * cfg["seq"] * cfg["hidden"] < (1 << 26)
 
 
 class _PrefixedFlat:

@@ -275,3 +275,10 @@ def test_elementwise_building_block_argument_rules():
     _lib.forge_swiglu_fwd(None, None, 0, 16, 0)
     _lib.forge_rope_apply(None, 64, None, None, None, 0, 4, 2, 32, 0, 0)
     assert _lib.forge_rmsnorm_bwd_workspace_bytes(4096, 4096) % (4096 * 4) == 0
+
+
+@pytest.mark.parametrize("tokens,hidden,side", [
+    (1024, 1016, False), (1024, 1024, True), (16384, 4088, True), (16384, 4096, False)])
+def test_side_streams_between_small_and_chip_filling_layers(tokens, hidden, side):
+    from paper_2609_13645_amd import runtime
+    assert runtime.uses_side_streams(dict(batch=1, seq=tokens, hidden=hidden)) is side
