@@ -6,6 +6,8 @@ the HIP kernels.
 """
 from __future__ import annotations
 
+import math
+
 import numpy as np
 
 from . import _lib
@@ -99,7 +101,7 @@ class FlatParams:
 
     def view(self, buf, name):
         off, shape = self.offsets[name]
-        return buf[off:off + int(np.prod(shape))].view(shape)
+        return buf[off:off + math.prod(shape)].view(shape)
 
     def load_bits(self, name, bits):
         """Set a parameter from bf16 bits; the master copy is its exact fp32 value."""
