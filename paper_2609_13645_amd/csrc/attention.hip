@@ -631,18 +631,6 @@ __device__ __forceinline__ void dma_16(const void* base, int bytes, uint4* lds, 
       __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, bytes, 0x00020000),
       (lds_ptr_t)lds, 16, off, 0, 0, 0);
 }
-// What is left of a matrix from a row on: its address and bytes.
-struct Rest {
-  const char* p;
-  int n;
-  __device__ __forceinline__ Rest(const bf16_t* base, long bytes)
-      : p(reinterpret_cast<const char*>(base)),
-        n(bytes <= 0 ? 0 : bytes > 0x7FFFFFF0L ? 0x7FFFFFF0 : (int)bytes) {}
-  __device__ __forceinline__ void skip(int step) {
-    p += step;
-    n = n > step ? n - step : 0;
-  }
-};
 __device__ __forceinline__ void dma_4(const float* base, uint4* lds, uint32_t off) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc(base), (lds_ptr_t)lds, 4, off, 0, 0, 0);
 }
@@ -701,7 +689,7 @@ __device__ __forceinline__ void kv_reduce_store(const f32x16_t (&acc)[D / 32][2]
   }
 }
 
-// Per pair: S, P = exp2(S c - LSE log2 e), dP, dS = P (dP + (-delta)) stored,
+// Per pair: S, P = exp2(S c - LSE log2 e), dP - delta, dS = P (dP - delta) stored,
 // dV^T += dO^T P, dK^T += Q^T dS. The block's K and V rows are held as two 32-key
 // column blocks, so every Q / dO fragment read from LDS feeds two MFMAs. dK comes
 // from the dS just formed: as a pass of its own it read the whole stored dS once
@@ -712,8 +700,9 @@ __device__ __forceinline__ void kv_reduce_store(const f32x16_t (&acc)[D / 32][2]
 // reloaded K fragments from scratch between the MFMAs.
 // dV and dK together, alone: 4 x 4096 tokens, 16 / 8 heads of 128, 885 us as two
 // passes (605 + 280, each pair's products and vector work one after the other),
-// 671 here; 16384 tokens, 32 / 8 heads, 6.52 ms and 5.10; 4 x 2047 tokens, 32 / 8
-// heads of 64, 337 us and 240.
+// 606 here (651 with every DMA instruction's address formed anew); 16384 tokens,
+// 32 / 8 heads, 6.52 ms and 4.62 (4.86); 4 x 2047 tokens, 32 / 8 heads of 64,
+// 337 us and 214 (240).
 template <int D>
 constexpr bool kVInLds = D == 128;
 
@@ -724,20 +713,31 @@ constexpr int kv_extra(int i) {
 }
 // LDS reads issued after those that step i waits for: ahead of step 0 the first
 // w fragments and the K fragments of steps 0 and 1; at the end of step j fragment
-// j + w (two reads where it is transposed), then the K or V of step j + 2.
+// j + w (two reads where it is transposed), then the K or V of step j + 2 and,
+// two steps before dP, the four reads of -delta.
 template <int D>
 constexpr int kv_behind(int i, int nst, int w) {
-  int n = 0;
-  for (int f = i + 1; f < i + w; ++f)
-    if (f < nst) n += f < D / 8 ? 1 : 2;
-  if (kv_extra<D>(i) == 0) {
-    for (int j = i - w; j < i; ++j)
-      if (j >= 0) n += kv_extra<D>(j + 2);
-    return n;
+  constexpr int KK = D / 16;
+  const auto frag = [=](int f) { return f >= nst ? 0 : f < 2 * KK ? 1 : 2; };
+  const int late = i == KK - 1 ? 4 : 0;
+  if (i == 0 && kv_extra<D>(0) > 0) return kv_extra<D>(1);
+  if (kv_extra<D>(i) > 0 || i == KK) return frag(i - 1 + w) + kv_extra<D>(i + 1) + late;
+  int n = late;
+  for (int f = i + 1; f < i + w; ++f) n += frag(f);
+  for (int j = i - w; j < i; ++j)
+    if (j >= 0) n += kv_extra<D>(j + 2);
+  return n;
+}
+// Sixteen floats of four 16-byte pieces.
+__device__ __forceinline__ f32x16_t rows16(const bf16x8_t (&r)[4]) {
+  f32x16_t x;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const f32x4_t v = __builtin_bit_cast(f32x4_t, r[g]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[g * 4 + e] = v[e];
   }
-  if (i == 0) return kv_extra<D>(1);
-  const int f = i - 1 + w;
-  return (f < nst ? (f < D / 8 ? 1 : 2) : 0) + kv_extra<D>(i + 1);
+  return x;
 }
 
 template <int D>
@@ -814,8 +814,8 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_kv_k(AttnArgs a,
       const int t = i / P::PER, row = (i % P::PER) * P::RPI + lane / P::LPR;
       const int r0 = k0 + (t == 1 ? 32 : 0);
       const bf16_t* src = t == 2 ? a.k : a.v;
-      const Rest left(src + (rb + r0) * a.ld_qkv + (long)m * D, (long)(S - r0) * a.ld_qkv * 2);
-      dma_16(left.p, left.n, vt + i * 64,
+      const int rows = S - r0 < 0 ? 0 : S - r0 < 32 ? S - r0 : 32;
+      dma_16(src + (rb + r0) * a.ld_qkv + (long)m * D, rows * (int)(a.ld_qkv * 2), vt + i * 64,
              (uint32_t)(((long)row * a.ld_qkv + ((lane % P::LPR) ^ fsw<D>(row)) * 8) * 2));
     }
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
@@ -829,43 +829,49 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_kv_k(AttnArgs a,
   // so the blocks running at once read the same Q / dO slabs (one XCD's L2
   // serves them; block ids cycle through the kv heads, which the dispatcher
   // spreads over the XCDs).
+  // (walked without a division or a product: head, slab and the addresses of
+  // their rows advance by the step's)
   struct Pair {
     int n, q0;
+    const char *q, *o;   // the pair's rows of Q and dO
   };
-  // (walked without a division: head and slab advance by the step's)
   const int p0 = wave + 4 * kb_.z, step = 4 * splits;
   const int step_n = step % grp, step_q = step / grp * BQ;
+  const int qrb = (int)(a.ld_qkv * 2), orb = (int)(ldo * 2);   // bytes of a row
+  const long q_adv = (long)step_n * D * 2 - (long)step_q * qrb;
+  const long o_adv = (long)step_n * D * 2 - (long)step_q * orb;
+  const long q_wrap = q_adv - (long)grp * D * 2 - (long)BQ * qrb;
+  const long o_wrap = o_adv - (long)grp * D * 2 - (long)BQ * orb;
   auto pair_at = [&](int p) __attribute__((always_inline)) {
-    return Pair{m * grp + p % grp, (j0 + ns - 1 - p / grp) * BQ};
+    const int n = m * grp + p % grp, q0 = (j0 + ns - 1 - p / grp) * BQ;
+    return Pair{n, q0,
+                reinterpret_cast<const char*>(a.q + (rb + q0) * a.ld_qkv + (long)n * D),
+                reinterpret_cast<const char*>(dout + (rb + q0) * ldo + (long)n * D)};
   };
   auto advance = [&](Pair w) __attribute__((always_inline)) {
     w.n += step_n;
     w.q0 -= step_q;
-    if (w.n >= (m + 1) * grp) {
-      w.n -= grp;
-      w.q0 -= BQ;
-    }
+    const bool wrap = w.n >= (m + 1) * grp;
+    w.q += wrap ? q_wrap : q_adv;
+    w.o += wrap ? o_wrap : o_adv;
+    w.n -= wrap ? grp : 0;
+    w.q0 -= wrap ? BQ : 0;
     return w;
   };
   // DMA instruction I of a pair into a buffer: the Q slab, the dO slab, then
   // (lanes 0-31) -LSE log2(e) and (lanes 32-63) -delta of the slab's queries
-  struct Slabs {
-    Rest q, o;
-  };
-  const int qstep = P::RPI * (int)a.ld_qkv * 2, ostep = P::RPI * (int)ldo * 2;
-  auto slabs = [&](const Pair& w) __attribute__((always_inline)) {
-    return Slabs{Rest(a.q + (rb + w.q0) * a.ld_qkv + (long)w.n * D, (long)(S - w.q0) * a.ld_qkv * 2),
-                 Rest(dout + (rb + w.q0) * ldo + (long)w.n * D, (long)(S - w.q0) * ldo * 2)};
-  };
-  auto dma = [&](auto I, const Pair& w, Slabs& sl, uint4* base) __attribute__((always_inline)) {
+  // (z: a zero the compiler cannot see through; the offsets of all instructions,
+  // hoisted out of the loop, would not fit the registers)
+  auto dma = [&](auto I, const Pair& w, uint32_t z, uint4* base) __attribute__((always_inline)) {
     constexpr int i = I;
+    const int rows = S - w.q0 < BQ ? S - w.q0 : BQ;
     if constexpr (i < P::PER) {
-      dma_16(sl.q.p, sl.q.n, base + i * 64, qrow + (c0 ^ fsw<D>(i * P::RPI) * 16));
-      sl.q.skip(qstep);
+      dma_16(w.q, rows * qrb, base + i * 64,
+             qrow + (c0 ^ fsw<D>(i * P::RPI) * 16) + (i * P::RPI * qrb + z));
     } else if constexpr (i < 2 * P::PER) {
       constexpr int j = i - P::PER;
-      dma_16(sl.o.p, sl.o.n, base + SLAB + j * 64, orow + (c0 ^ fsw<D>(j * P::RPI) * 16));
-      sl.o.skip(ostep);
+      dma_16(w.o, rows * orb, base + SLAB + j * 64,
+             orow + (c0 ^ fsw<D>(j * P::RPI) * 16) + (j * P::RPI * orb + z));
     } else {
       const long li = ((long)b * a.n_heads + w.n) * S + w.q0 + l32;
       dma_4(delta, base + 2 * SLAB,
@@ -885,8 +891,11 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_kv_k(AttnArgs a,
   //   dP    the probabilities of the first 16 queries (and, at D = 128, four
   //         scores of the rest), from the third MFMA on, when S is complete
   //   dV 1  the remaining probabilities
-  //   dV 2  dS = P (dP - delta), packed; the second 16 queries' under the
-  //         first half of dK
+  //   dV 2  dS = P (dP - delta), its bracket the accumulators that started from
+  //         -delta, packed; the second 16 queries' under the first half of dK
+  // What bounds it is the rate at which one wave issues (about one instruction
+  // in five cycles): hence addresses that advance instead of being formed anew
+  // for every pair and DMA instruction, and no subtraction of delta of its own.
   // Fragments are read W steps ahead (inline asm with counted waits). As three
   // separate phases (products, then all probabilities and dS, then dV) the
   // matrix unit stood still during the second.
@@ -913,13 +922,14 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_kv_k(AttnArgs a,
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     __builtin_amdgcn_sched_barrier(0);
     const int q0 = w.q0;
-    Slabs sl = slabs(wn);
+    const uint32_t z = 0;
     // (opaque, so that the sums with it stay at the reads: hoisted out of the
     // loop for both buffers they take 32 registers that the kernel lacks)
     uint32_t ab = fa::lds_off(base);
     asm volatile("" : "+v"(ab));
-    // -LSE log2(e), later -delta, of the lane's queries 8 g + 4 hh + {0..3}
-    bf16x8_t row[4];
+    // -LSE log2(e) and -delta (which dP's accumulators start from) of the
+    // lane's queries 8 g + 4 hh + {0..3}
+    bf16x8_t row[4], nd[4];
     constexpr int LO = 2 * SLAB * 16;
     const uint32_t lb = ab + hh * 16;
     static_for<4>([&](auto G) __attribute__((always_inline)) {
@@ -964,11 +974,10 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_kv_k(AttnArgs a,
     // blocks, then the others
     auto dscore = [&](auto H) __attribute__((always_inline)) {
       constexpr int kb = (H / 2) % 2, u = H / 4, i = u * 8 + (H % 2) * 4;
-      const f32x4_t nd = __builtin_bit_cast(f32x4_t, row[i >> 2]);
       float v[4];
       static_for<4>([&](auto E) __attribute__((always_inline)) {
         constexpr int e = E;
-        v[e] = sc[kb][i + e] * (dp[kb][i + e] + nd[e]);
+        v[e] = sc[kb][i + e] * dp[kb][i + e];
       });
       const uint32_t w0 = pack2(v[0], v[1]), w1 = pack2(v[2], v[3]);
       dsp[2 * kb + u][(H % 2) * 2] = w0;
@@ -983,7 +992,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_kv_k(AttnArgs a,
         }
         constexpr int i0 = B::DMA * x / (2 * KK), i1 = B::DMA * (x + 1) / (2 * KK);
         static_for<i1 - i0>([&](auto V) __attribute__((always_inline)) {
-          dma(fa::ic<i0 + V>{}, wn, sl, next);
+          dma(fa::ic<i0 + V>{}, wn, z, next);
         });
       } else if constexpr (x < 4 * KK) {
         constexpr int N = 2 * KK - 2, t = x - 2 * KK - 2;
@@ -1016,16 +1025,15 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_kv_k(AttnArgs a,
     }
     static_for<NST>([&](auto I) __attribute__((always_inline)) {
       constexpr int i = I;
-      // (at the first step of the last phases every read has to have returned,
-      // the -delta rows just issued among them)
-      fa::wait_lds<i == 2 * KK + DB ? 0 : kv_behind<D>(i, NST, W)>();
+      fa::wait_lds<kv_behind<D>(i, NST, W)>();
       fa::bind(fr[i % W]);
       if constexpr (kv_extra<D>(i) > 0) fa::bind(vr[i % 2][0]);
       if constexpr (kv_extra<D>(i) > 1) fa::bind(vr[i % 2][1]);
-      if constexpr (i == 0 || i == 2 * KK + DB) {
-        static_for<4>([&](auto G) __attribute__((always_inline)) {
-          fa::bind(row[G]);
-        });
+      if constexpr (i == 0) {
+        static_for<4>([&](auto G) __attribute__((always_inline)) { fa::bind(row[G]); });
+      }
+      if constexpr (i == KK) {
+        static_for<4>([&](auto G) __attribute__((always_inline)) { fa::bind(nd[G]); });
       }
       static_for<2>([&](auto KB) __attribute__((always_inline)) {
         constexpr int kb = KB;
@@ -1036,9 +1044,9 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_kv_k(AttnArgs a,
             sc[kb] = MFMA(fr[i % W], kf[kb][i], i == 0 ? f32x16_t{} : sc[kb]);
         } else if constexpr (i < 2 * KK) {
           if constexpr (VL)
-            dp[kb] = MFMA(fr[i % W], vr[i % 2][kb], i == KK ? f32x16_t{} : dp[kb]);
+            dp[kb] = MFMA(fr[i % W], vr[i % 2][kb], i == KK ? rows16(nd) : dp[kb]);
           else
-            dp[kb] = MFMA(fr[i % W], vf[kb][i - KK], i == KK ? f32x16_t{} : dp[kb]);
+            dp[kb] = MFMA(fr[i % W], vf[kb][i - KK], i == KK ? rows16(nd) : dp[kb]);
         } else {
           constexpr int db = (i - 2 * KK) % DB, g = (i - 2 * KK) / DB;
           if constexpr (g < 2)
@@ -1050,6 +1058,10 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_kv_k(AttnArgs a,
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (kb == 1 && i + W < NST) read(fa::ic<i + W>{});
         if constexpr (VL && kb == 1 && i + 2 < 2 * KK) read_kv(fa::ic<i + 2>{});
+        if constexpr (kb == 1 && i == KK - 2)
+          static_for<4>([&](auto G) __attribute__((always_inline)) {
+            nd[G] = fa::rd_b128<LO + BQ * 4 + G * 32>(lb);
+          });
         // causal mask and sequence tail (diagonal and last slabs only), once S
         // is complete: -inf scores, so exp2 gives 0
         if constexpr (i == KK && kb == 0) {
@@ -1064,11 +1076,6 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_kv_k(AttnArgs a,
           }
         }
         under(fa::ic<2 * i + kb>{});
-        // the probabilities are done with the LSE rows: -delta takes their place
-        if constexpr (i == 2 * KK + DB - 1 && kb == 1)
-          static_for<4>([&](auto G) __attribute__((always_inline)) {
-            row[G] = fa::rd_b128<LO + BQ * 4 + G * 32>(lb);
-          });
         __builtin_amdgcn_sched_barrier(0);
       });
     });
@@ -1079,8 +1086,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_kv_k(AttnArgs a,
   uint4* mine = sm + wave * 2 * B::WBUF;
   int cur = 0;
   Pair w = pair_at(min(p0, total - 1));
-  Slabs first = slabs(w);
-  static_for<B::DMA>([&](auto I) __attribute__((always_inline)) { dma(I, w, first, mine); });
+  static_for<B::DMA>([&](auto I) __attribute__((always_inline)) { dma(I, w, 0, mine); });
   for (int p = p0; p < total; p += step) {
     const Pair wn = p + step < total ? advance(w) : w;
     pair(mine + cur * B::WBUF, w, mine + (cur ^ 1) * B::WBUF, wn);
