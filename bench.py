@@ -96,10 +96,10 @@ def kc_kernel_name(M, N, suffix):
     both operands K-contiguous (for labelling the roofline kernel only): full
     256 x 256 tiles on the ring pipeline, with a last round at most half full
     run as 256 x 128 halves in a second launch; 256 x 192 when that fills the
-    last wave of workgroups better; smaller tiles for small problems.
-    `suffix` closes each template argument list."""
+    last wave of workgroups better; below a chip of 256 x 256 tiles the
+    library's cost estimate picks the tile (and splits), which is not repeated
+    here. `suffix` closes each template argument list."""
     big = -(-M // 256) * -(-N // 256)
-    mid = -(-M // 256) * -(-N // 128)
     if big >= 256:
         tail = big % 256
         if big > 256 and 0 < tail <= 128:
@@ -109,7 +109,7 @@ def kc_kernel_name(M, N, suffix):
         c192 = -(-t192 // 256) * 192.0 / 0.74
         head = "gemm_kernel<256,192,4,2" if c192 < c256 else "ring_kernel<256,256,2,4"
     else:
-        head = "gemm_kernel<256,128,2,2" if mid >= 256 else "gemm_kernel<128,128,2,2"
+        return "ring_kernel / wave_kernel (tile by estimated cost)"
     return head + suffix
 
 
@@ -696,7 +696,7 @@ def step_timeline(db_path, which=2, out=sys.stdout):
         short = re.sub(r"\(.*", "", name.replace("void ", "").replace(
             "forge::(anonymous namespace)::", ""))
         rows.append((short, gx // max(1, wx), start, end, stream))
-    gemm, rope = ("gemm_kernel", "ring_kernel"), ("rope_apply", "qknorm_rope")
+    gemm, rope = ("gemm_kernel", "ring_kernel", "wave_kernel"), ("rope_apply", "qknorm_rope")
     # the QKV product is one launch, or two when its last round runs as halves
     starts = [i for i in range(len(rows) - 3) if rows[i][0].startswith("rmsnorm_fwd")
               and rows[i + 1][0].startswith(gemm)
