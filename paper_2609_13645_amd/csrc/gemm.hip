@@ -1066,7 +1066,10 @@ constexpr int kCUs = 256;
 //   fixed + round * (rounds - 1) + K * (per_k + full_k * share of CUs busy) * rounds
 // microseconds, rounds counted over the tiles resident at once (`slots`: two
 // workgroups of the four-wave tiles share a CU; a last round that gives every
-// CU at most one of them costs `half`). The constants are a fit (10-15 % rms)
+// CU at most one of them costs `half`; one that gives some two costs a whole one,
+// except with both operands K-contiguous at 128 x 128, whose kernel's cost rises
+// evenly: with K 4096 45 us at 256 tiles, 50 at 288, 53 at 320, 60 at 384,
+// and 51, 52, 54, 57 on 128 x 256). The constants are a fit (10-15 % rms)
 // to 130 products, M, N in 64..16384, K in 64..16384, all layouts, timed on
 // every tile: the pick is on average 2 % slower than the fastest tile, and
 // 1.47 times as fast as one threshold on the number of tiles (256 x 256 from
@@ -1093,7 +1096,12 @@ long tile_count(int t, long M, long N) {
 double tile_cost(int layout, int t, long tiles, long K) {
   const TileCost& c = kCost[layout][t];
   const long full = tiles / kSlots[t], rem = tiles % kSlots[t];
-  const double part = rem == 0 ? 0.0 : (rem <= kCUs ? kHalfRound[t] : 1.0);
+  const double half = kHalfRound[t];
+  const double part = rem == 0      ? 0.0
+                      : rem <= kCUs ? half
+                      : t == kT128 && layout == 0
+                          ? half + (1.0 - half) * (double)(rem - kCUs) / kCUs
+                          : 1.0;
   const double busy = (double)(tiles < kCUs ? tiles : kCUs) / kCUs;
   return c.fixed + kRound[t] * (double)(full + (rem > 0) - 1) +
          (double)K * (c.per_k + c.full_k * busy) * ((double)full + part);

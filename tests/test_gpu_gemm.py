@@ -151,7 +151,8 @@ def test_gemm_split_last_round_integer_exact(M, N, K, epi):
 # directions), 128 x 128, 128 x 256, 256 x 256
 @pytest.mark.parametrize("la,lb,epi", COMBOS)
 @pytest.mark.parametrize("M,N,K", [(64, 64, 32), (72, 56, 104), (1000, 264, 2056), (2056, 1032, 296),
-                                   (3080, 1032, 1000), (2056, 2040, 2072), (3840, 4088, 1032)])
+                                   (3080, 1032, 1000), (2056, 2040, 2072), (3840, 4088, 1032),
+                                   (5000, 1000, 520)])   # 320 tiles of 128 x 128: a partly shared round
 def test_gemm_tile_choice_integer_exact(la, lb, epi, M, N, K):
     banner(f"gemm int tile choice la={la} lb={lb} epi={epi} M={M} N={N} K={K}")
     got, ref = run_gemm(la, lb, epi, M, N, K, seed=M + N + K + epi)
