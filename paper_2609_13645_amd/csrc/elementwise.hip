@@ -452,30 +452,20 @@ __global__ void embed_fwd_k(const int32_t* __restrict__ ids, const bf16_t* __res
   *reinterpret_cast<uint4*>(x + t * h + c * 8) = val;
 }
 
-// dE[id] += scale * dx. A wave takes 512 columns of a token, lane l the columns
-// l, l + 64, ..: each atomic instruction adds 64 consecutive floats, two whole
-// 128-byte lines (eight consecutive columns per lane touched all sixteen lines
-// in each of its eight instructions: 2048 x 2048 took 112 us, now 19).
-__global__ __launch_bounds__(256) void embed_bwd_k(const int32_t* __restrict__ ids,
-                                                   const bf16_t* __restrict__ dx,
-                                                   float* __restrict__ demb, int T, int h, int V,
-                                                   float scale) {
-  const int lane = threadIdx.x & 63;
-  const int cpr = (h + 511) / 512;
-  const long id = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
+__global__ void embed_bwd_k(const int32_t* __restrict__ ids, const bf16_t* __restrict__ dx,
+                            float* __restrict__ demb, int T, int h, int V, float scale) {
+  const int cpr = h / 8;
+  const long id = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (id >= (long)T * cpr) return;
   const long t = id / cpr;
-  const int c0 = (int)(id % cpr) * 512 + lane;
+  const int c = (int)(id % cpr);
   const int v = ids[t];
   if (v < 0 || v >= V) return;
-  const bf16_t* src = dx + t * h;
   float f[8];
+  unpack8(*reinterpret_cast<const uint4*>(dx + t * h + c * 8), f);
+  float* dst = demb + (long)v * h + c * 8;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) f[e] = c0 + e * 64 < h ? bf2f(src[c0 + e * 64]) : 0.0f;
-  float* dst = demb + (long)v * h;
-#pragma unroll
-  for (int e = 0; e < 8; ++e)
-    if (c0 + e * 64 < h) unsafeAtomicAdd(dst + c0 + e * 64, f[e] * scale);
+  for (int e = 0; e < 8; ++e) unsafeAtomicAdd(dst + e, f[e] * scale);
 }
 
 // ------------------------------------------------------- cross-entropy ----
@@ -799,9 +789,9 @@ hipError_t embed_fwd(const int32_t* ids, const uint16_t* emb, uint16_t* x, int T
 
 hipError_t embed_bwd(const int32_t* ids, const uint16_t* dx, float* demb, int T, int h, int V,
                      float scale, hipStream_t s) {
-  const long n = (long)T * ((h + 511) / 512);
+  const long n = (long)T * (h / 8);
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(embed_bwd_k, dim3(blocks_for(n, 4)), dim3(256), 0, s, ids, dx, demb, T, h, V,
+  hipLaunchKernelGGL(embed_bwd_k, dim3(blocks_for(n, 256)), dim3(256), 0, s, ids, dx, demb, T, h, V,
                      scale);
   return hipGetLastError();
 }
