@@ -396,8 +396,9 @@ forge_status forge_embed_fwd(const int32_t* ids, const forge_bf16* emb, forge_bf
                              forge_stream stream);
 
 /* d_emb[ids[t], :] += scale * dx0[t, :] (fp32 +=). Ids outside [0, V) are
- * skipped. Uses fp32 atomics: the summation order over repeated ids varies
- * between runs (not bit-deterministic). */
+ * skipped. No atomics: the rows of a repeated id are added in a fixed order,
+ * so the result repeats bit for bit. As with the other gradients, calls that
+ * add to the same d_emb have to be ordered by the caller. */
 forge_status forge_embed_bwd(const int32_t* ids, const forge_bf16* dx0, float* d_emb,
                              int32_t tokens, int32_t hidden, int32_t vocab, float scale,
                              forge_stream stream);

@@ -121,9 +121,10 @@ def test_embedding_fwd_bwd():
     assert rel_fro(host_f64(dE), ref) <= 1e-6
 
 
-@pytest.mark.parametrize("T,h", [(1, 8), (5, 504), (3, 512), (7, 520), (130, 1032), (2, 8192)])
+@pytest.mark.parametrize("T,h", [(1, 8), (5, 504), (3, 512), (7, 520), (130, 1032), (2, 8192),
+                                 (9, 56), (9, 64), (9, 72)])
 def test_embedding_bwd_column_edges(T, h):
-    """Widths around the 512 columns a wave adds: every column of a token once,
+    """Widths around the 64 columns a workgroup adds: every column of a token once,
     onto what the gradient holds, none of the neighbouring rows."""
     import torch
     from paper_2609_13645_amd import _lib
@@ -139,3 +140,60 @@ def test_embedding_bwd_column_edges(T, h):
     ref = base.astype(np.float64)
     np.add.at(ref, ids, 0.5 * fi.bf16_bits_to_f64(dxb))
     assert np.array_equal(host_f64(dE), ref)   # small multiples of 1/2: exact
+
+
+def _ids(kind, T, V, rng):
+    """Token ids that fill the 32 (from 8193 tokens up more) slices of the
+    embedding gradient in different ways."""
+    if kind == "one":            # one id: a single run over all the cuts
+        return np.full(T, 7, np.int32)
+    if kind == "slice":          # every token in one slice, few tokens per id
+        return (rng.integers(0, V // 128, T) * 128 + 5).astype(np.int32)
+    if kind == "distinct":       # every id once
+        return rng.permutation(V)[:T].astype(np.int32)
+    return np.minimum(rng.zipf(1.3, T) - 1, V).astype(np.int32)   # "text" (some out of range: V)
+
+
+# one slice's tokens around the 256 that are ranked, the 32 of a piece and the
+# 2048 that are sorted at once
+@pytest.mark.parametrize("kind,T", [("one", 33), ("one", 64), ("one", 257), ("one", 2048), ("one", 2049),
+                                    ("one", 6000), ("slice", 255), ("slice", 256), ("slice", 257),
+                                    ("slice", 2047), ("slice", 5000), ("distinct", 9000),
+                                    ("text", 2100), ("text", 20000)])
+def test_embedding_bwd_repeats_bit_for_bit(kind, T):
+    """Repeated ids: the exact sums of small integers, and for normal values the
+    same bits in every run (whatever order the workgroups come in), within the
+    rounding of fp32 sums of the float64 result."""
+    import torch
+    from paper_2609_13645_amd import _lib
+    banner(f"embedding bwd {kind} T={T}")
+    rng = np.random.default_rng(T)
+    h, V = 200, 16384
+    ids = _ids(kind, T, V, rng)
+    ok = (ids >= 0) & (ids < V)
+    ids_d = torch.from_numpy(ids).cuda()
+
+    def run(bits, base):
+        d = torch.from_numpy(base.copy()).cuda()
+        _lib.forge_embed_bwd(ids_d, bits, d, T, h, V)
+        torch.cuda.synchronize()
+        return d
+
+    base = rng.integers(-8, 9, (V, h)).astype(np.float32)
+    small = rng.integers(-8, 9, (T, h)).astype(np.float32)
+    ref = base.astype(np.float64)
+    np.add.at(ref, ids[ok], small[ok].astype(np.float64))
+    assert np.array_equal(host_f64(run(dev_bf16(fi.to_bf16_bits(small)), base)), ref)
+
+    xb = fi.to_bf16_bits(rng.standard_normal((T, h), dtype=np.float32))
+    first = run(dev_bf16(xb), base)
+    for _ in range(4):
+        assert torch.equal(run(dev_bf16(xb), base), first)
+    ref = base.astype(np.float64)
+    size = np.abs(ref)
+    x = fi.bf16_bits_to_f64(xb)[ok]
+    np.add.at(ref, ids[ok], x)
+    np.add.at(size, ids[ok], np.abs(x))
+    # sums of n fp32 terms in any order: at most (n - 1) roundings of the terms' total
+    n = 1 + np.bincount(ids[ok], minlength=V)[:, None]
+    assert np.all(np.abs(host_f64(first) - ref) <= n * 2.0 ** -24 * size)
