@@ -41,12 +41,14 @@
 //    four consecutive accumulator rows are four consecutive n of one row m of
 //    C: the epilogue writes 16-byte fp32 vectors, and in the ring kernel
 //    lanes l and l ^ 16 swap halves so that each writes eight consecutive
-//    bf16 (one 16-byte nontemporal store). The AdamW epilogues of the grouped
+//    bf16 (one 16-byte store). The AdamW epilogues of the grouped
 //    weight gradients stage the fp32 tile through the free stage ring and
 //    stream it by rows through the optimizer state (adam_tile).
 //  * Workgroups are dispatched round-robin over the 8 XCDs; the tile order is
 //    remapped so each XCD works on a contiguous, M-grouped band of tiles and
 //    reuses operands in its own L2.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -511,10 +513,14 @@ __device__ __forceinline__ void wait_dma() {
 }
 
 // ---- bf16 epilogue: eight consecutive n of row m ---------------------------
-// A full piece is one 16-byte nontemporal store (see store4): with whole
-// 16-byte pieces, 64 contiguous bytes per row and instruction, streaming
-// stores keep the XCD's L2 for the operand rows.
-template <int EPI>
+// A full piece is one 16-byte store, streaming (nontemporal, see store4) or
+// ordinary: 64 contiguous bytes per row and instruction, and where these are
+// whole 64-byte lines streaming stores keep the XCD's L2 for the operand rows.
+// Rows that do not start on a line straddle two in every instruction; streamed,
+// each half goes to memory by itself, while ordinary stores meet in L2. N 6120
+// (2144 x 6120 x 208, K-contiguous) streamed 29.1 us, ordinary 18.0; N 6144
+// streamed 14.6, ordinary 16.5.
+template <int EPI, bool STREAM>
 __device__ __forceinline__ void store8_bf16(const GemmArgs& p, int m, int n, float* x) {
   if (m >= p.M) return;
 #pragma unroll
@@ -534,7 +540,9 @@ __device__ __forceinline__ void store8_bf16(const GemmArgs& p, int m, int n, flo
     }
   }
   if (full) {
-    __builtin_nontemporal_store(__builtin_bit_cast(f32x4_t, pack8(x)), reinterpret_cast<f32x4_t*>(C));
+    const f32x4_t v = __builtin_bit_cast(f32x4_t, pack8(x));
+    if (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<f32x4_t*>(C));
+    else *reinterpret_cast<f32x4_t*>(C) = v;
   } else {
     for (int e = 0; e < 8; ++e)
       if (n + e < p.N) C[e] = f2bf(x[e]);
@@ -603,29 +611,39 @@ __device__ __forceinline__ void adam_store(const GemmArgs& p, const float* sc, i
   }
 }
 
-template <int EPI, int FN, int FM>
+// LINES: choose streaming or ordinary stores by the rows of C (else streaming).
+// Once for the tile: a branch at every piece costs 1.4 us of 15. Four-wave tiles
+// stream always: with both forms the compiler copies their accumulators around
+// (128 x 128, K 2048: 66 -> 76 us).
+template <int EPI, bool LINES, int FN, int FM>
 __device__ __forceinline__ void store_tile16(const GemmArgs& p, const f32x4_t (&acc)[FN][FM],
                                              int mw, int nw, int lane) {
   if constexpr (EPI == kStoreBF16 || EPI == kResidBF16) {
     static_assert(FN % 2 == 0, "bf16 epilogue pairs neighbouring n-blocks");
     const int g = lane >> 4;
     const bool even = (g & 1) == 0;
+    auto store = [&](auto STREAM) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < FN; i += 2)
+      for (int i = 0; i < FN; i += 2)
 #pragma unroll
-      for (int j = 0; j < FM; ++j) {
-        const int m = mw + j * 16 + (lane & 15);
-        float x[8];
+        for (int j = 0; j < FM; ++j) {
+          const int m = mw + j * 16 + (lane & 15);
+          float x[8];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float send = even ? acc[i + 1][j][e] : acc[i][j][e];
-          const float recv = __shfl_xor(send, 16);
-          x[e] = even ? acc[i][j][e] : recv;
-          x[4 + e] = even ? recv : acc[i + 1][j][e];
+          for (int e = 0; e < 4; ++e) {
+            const float send = even ? acc[i + 1][j][e] : acc[i][j][e];
+            const float recv = __shfl_xor(send, 16);
+            x[e] = even ? acc[i][j][e] : recv;
+            x[4 + e] = even ? recv : acc[i + 1][j][e];
+          }
+          const int n = nw + (even ? i * 16 + g * 4 : (i + 1) * 16 + (g - 1) * 4);
+          store8_bf16<EPI, decltype(STREAM)::value>(p, m, n, x);
         }
-        const int n = nw + (even ? i * 16 + g * 4 : (i + 1) * 16 + (g - 1) * 4);
-        store8_bf16<EPI>(p, m, n, x);
-      }
+    };
+    if (!LINES || ((reinterpret_cast<uintptr_t>(p.C) | (uintptr_t)(p.ldc * 2)) & 63) == 0)
+      store(std::true_type());
+    else
+      store(std::false_type());
   } else {
 #pragma unroll
     for (int i = 0; i < FN; ++i)
@@ -814,7 +832,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 1) void ring_kernel(GemmArgs
     adam_tile<BM, BN, WAVES_M, WAVES_N, EPI, FN, FM>(p, acc, reinterpret_cast<float*>(lds), m0,
                                                       n0, wm, wn, wave, lane);
   } else {
-    store_tile16<EPI, FN, FM>(p, acc, m0 + wm * WM, n0 + wn * WN, lane);
+    store_tile16<EPI, NW == 8, FN, FM>(p, acc, m0 + wm * WM, n0 + wn * WN, lane);
   }
 }
 

@@ -190,6 +190,38 @@ def test_gemm_odd_rows_and_columns_integer_exact(epi, M, N, K):
     assert np.array_equal(host_f64(C), want)
 
 
+# one and several 256 x 256 tiles, 128 x 256, 128 x 128 and 64 x 64 ones
+@pytest.mark.parametrize("M,N,K", [(4096, 4096, 32), (4000, 4008, 40), (2048, 2560, 72), (1024, 1000, 520),
+                                   (72, 56, 40)])
+@pytest.mark.parametrize("lb", [KC, MC])
+@pytest.mark.parametrize("epi", [STORE_BF16, RESID_BF16])
+@pytest.mark.parametrize("off,pad", [(0, 0), (8, 0), (0, 8), (24, 32)])
+def test_gemm_bf16_rows_on_and_off_64_byte_lines(M, N, K, lb, epi, off, pad):
+    """bf16 results whose rows start on 64-byte lines or not (C that starts
+    `off` elements behind a line, a leading dimension of N + pad): streaming
+    or ordinary stores, the same exact values and nothing beside them."""
+    import torch
+    from paper_2609_13645_amd import _lib
+    banner(f"gemm int lines M={M} N={N} K={K} lb={lb} epi={epi} off={off} pad={pad}")
+    rng = np.random.default_rng(M + N + off + pad)
+    A = torch.from_numpy(rng.integers(-4, 5, (M, K)).astype(np.float32)).cuda()
+    B = torch.from_numpy(rng.integers(-4, 5, (N, K) if lb == KC else (K, N)).astype(np.float32)).cuda()
+    ld = N + pad
+    buf = torch.full((off + M * ld + 8,), 3.0, dtype=torch.bfloat16, device="cuda")
+    assert buf.data_ptr() % 64 == 0
+    C = buf[off:off + M * ld]
+    R = torch.from_numpy(rng.integers(-8, 9, (M, N)).astype(np.float32)).cuda().bfloat16()
+    _lib.forge_gemm(KC, lb, epi, A.bfloat16(), B.bfloat16(), C, R if epi == RESID_BF16 else None,
+                    M, N, K, K, K if lb == KC else N, ld, N if epi == RESID_BF16 else 0)
+    torch.cuda.synchronize()
+    # |sum| <= 16 K + 8 < 2^24: exact in fp32 whatever the order
+    ref = A @ (B.T if lb == KC else B) + (R.float() if epi == RESID_BF16 else 0.0)
+    rows = C.view(M, ld)
+    assert torch.equal(rows[:, :N], ref.bfloat16())
+    assert bool((rows[:, N:] == 3.0).all()) and bool((buf[:off] == 3.0).all())
+    assert bool((buf[off + M * ld:] == 3.0).all())
+
+
 def test_gemm_zero_k_and_empty():
     banner("gemm K=0 / empty")
     got, ref = run_gemm(KC, KC, ACC_F32, 64, 64, 0)
