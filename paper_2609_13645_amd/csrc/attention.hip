@@ -1309,20 +1309,42 @@ size_t attn_bwd_ds_bytes(const AttnArgs& a) {
   return (size_t)a.batch * a.n_heads * DsLayout(a.seq).head * 2;
 }
 
-// Splits of a key-owned block's pairs. One block per 64 keys of a kv head
-// leaves CUs idle on short sequences with few kv heads (32 blocks at 1000
-// tokens and 2 kv heads), and below about 512 blocks the first key tile, with
-// twice the average work, is what the launch takes; splitting the pairs of a
-// block towards 512 blocks evens both out, for fp32 partial sums of dK and dV
-// that one more launch adds up. A wave keeps at least two pairs of the longest
-// block, and short launches (fewer than four) stay whole.
+// Splits of a key-owned block's pairs: the smallest estimate of the kv pass. One
+// workgroup per CU, so up to kCUs workgroups the pass takes its longest block
+// (the first key tile: every pair of its heads, over four waves), beyond that
+// the longest block or an even share of all of them (a key tile has half the
+// pairs on average). Each split adds a workgroup's start and reduction
+// (kBlockUs) per block, a second launch and its fp32 partials. Splitting pays
+// where one block is long and the launch leaves CUs idle (1 x 2023 tokens, 8 / 2
+// heads of 64, 64 blocks: 104 us unsplit, 60 split) and costs where there are
+// blocks enough or pairs few (1 x 546, 32 / 32 heads of 64, 288 blocks: 26.8
+// unsplit, 42.6 in two). Fitted to 90 shapes below 512 blocks, each timed with 1
+// to 16 splits: the pick is on average 0.5 % slower than the fastest (splitting
+// towards 512 blocks whatever their length: 7.4 %, never splitting: 9.3 %).
 static int kv_splits(const AttnArgs& a) {
+  constexpr double kCUs = 256.0, kLaunchUs = 1.1, kPartBytesPerUs = 3.6e6;
+  const double kPairUs = a.d == 128 ? 1.02 : 0.66, kBlockUs = a.d == 128 ? 3.2 : 6.4;
+  const long grp = a.n_heads / a.n_kv_heads;
   const long blocks = (long)((a.seq + 63) / 64) * a.n_kv_heads * a.batch;
-  const long pairs = (long)(a.n_heads / a.n_kv_heads) * ((a.seq + 31) / 32);
-  long z = (512 + blocks - 1) / blocks;
-  z = z < pairs / 8 ? z : pairs / 8;
-  z = z < 16 ? z : 16;
-  return pairs < 16 || z < 2 ? 1 : (int)z;
+  const long pairs = grp * ((a.seq + 31) / 32);
+  const double part = (double)a.batch * a.seq * a.n_kv_heads * a.d * 8.0;  // dK and dV of a split
+  int best = 1;
+  double cost = 0.0;
+  for (int z = 1; z <= 16; ++z) {
+    // (a wave keeps two pairs of the longest block; blocks * z below 512 + blocks
+    // bounds the partials by 64 MB)
+    if (z > 1 && (z * 8 > pairs || (z - 1) * blocks >= 512)) break;
+    const double longest = kBlockUs + kPairUs * (double)((pairs + 4 * z - 1) / (4 * z));
+    const double all = (double)blocks * (kBlockUs * z + kPairUs * (double)(pairs + grp) / 8.0);
+    double c = longest;
+    if ((double)blocks * z > kCUs && all / kCUs > c) c = all / kCUs;
+    if (z > 1) c += kLaunchUs + (z + 1) * part / kPartBytesPerUs;
+    if (z == 1 || c < cost) {
+      cost = c;
+      best = z;
+    }
+  }
+  return best;
 }
 
 size_t attn_bwd_part_bytes(const AttnArgs& a) {

@@ -277,6 +277,37 @@ def test_elementwise_building_block_argument_rules():
     assert _lib.forge_rmsnorm_bwd_workspace_bytes(4096, 4096) % (4096 * 4) == 0
 
 
+# longest block against launches that fill the chip: few blocks with many pairs
+# split, many blocks or few pairs do not
+@pytest.mark.parametrize("B,S,nh,nkv,d,splits", [
+    (1, 2023, 8, 2, 64, 5), (1, 1000, 16, 1, 128, 16), (1, 1000, 32, 2, 128, 13),
+    (2, 200, 4, 1, 128, 3), (1, 546, 32, 32, 64, 1), (4, 771, 8, 8, 128, 1),
+    (2, 1024, 32, 8, 64, 1), (1, 4096, 32, 8, 128, 1), (1, 128, 4, 2, 64, 1), (1, 1, 4, 1, 128, 1)])
+def test_attention_backward_splits(B, S, nh, nkv, d, splits):
+    up = lambda n: (n + 255) // 256 * 256
+    kt = (S + 63) // 64
+    slabs = sum((S + 31) // 32 - 2 * k for k in range(kt))     # 4 KB of dS each, per head
+    want = up(2 * B * nh * S * 4) + up(B * nh * slabs * 4096)
+    if splits > 1:
+        want += up(2 * splits * B * S * nkv * d * 4)
+    assert _lib.forge_attention_bwd_workspace_bytes(_lib.AttnCfg(B, S, nh, nkv, d)) == want
+
+
+def test_attention_backward_partials_are_bounded():
+    up = lambda n: (n + 255) // 256 * 256
+    for S in (1, 63, 64, 65, 500, 1000, 2049, 4096, 16000):
+        for B in (1, 3, 8):
+            for nkv in (1, 2, 5, 8, 32):
+                for g in (1, 3, 8):
+                    for d in (64, 128):
+                        kt, ns = (S + 63) // 64, (S + 31) // 32
+                        rest = up(2 * B * nkv * g * S * 4) + up(
+                            B * nkv * g * sum(ns - 2 * k for k in range(kt)) * 4096)
+                        n = _lib.forge_attention_bwd_workspace_bytes(
+                            _lib.AttnCfg(B, S, nkv * g, nkv, d))
+                        assert 0 <= n - rest <= 64 << 20, (B, S, nkv, g, d)
+
+
 @pytest.mark.parametrize("tokens,hidden,side", [
     (1024, 1016, False), (1024, 1024, True), (16384, 4088, True), (16384, 4096, False)])
 def test_side_streams_between_small_and_chip_filling_layers(tokens, hidden, side):

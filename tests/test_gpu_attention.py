@@ -28,6 +28,9 @@ CASES = [
     (1, 65, 4, 2, 128),
     (2, 95, 6, 2, 128),
     (1, 289, 9, 3, 64),
+    # enough blocks that none is split, several pairs per wave
+    (2, 700, 16, 16, 128),
+    (1, 546, 32, 32, 64),
 ]
 
 
