@@ -542,6 +542,28 @@ forge_status forge_gemm(int32_t layout_a, int32_t layout_b, int32_t epilogue,
                         forge_stream stream);
 
 /*
+ * The same product times alpha (C = alpha * acc, plus R or C), with scratch
+ * (16-byte aligned, scratch_bytes bytes, may be NULL with 0): where there are
+ * few output tiles and a long reduction, the reduction is split over more
+ * workgroups, whose fp32 partial products in scratch are added in order, as in
+ * the layers and the head, which pass a part of their workspace.
+ */
+forge_status forge_gemm_scratch(int32_t layout_a, int32_t layout_b, int32_t epilogue,
+                                const forge_bf16* A, const forge_bf16* B, void* C,
+                                const forge_bf16* R, int32_t M, int32_t N, int32_t K,
+                                int64_t lda, int64_t ldb, int64_t ldc, int64_t ldr, float alpha,
+                                void* scratch, size_t scratch_bytes, forge_stream stream);
+
+/*
+ * Host only: how a product of these sizes runs with this much scratch: the
+ * output tile, the splits of its reduction and the scratch bytes they take
+ * (0 for one split). Any out pointer may be NULL.
+ */
+forge_status forge_gemm_plan(int32_t layout_a, int32_t layout_b, int32_t M, int32_t N, int32_t K,
+                             size_t scratch_bytes, int32_t* tile_m, int32_t* tile_n,
+                             int32_t* splits, size_t* bytes);
+
+/*
  * Grouped products over row groups: the per-expert projections of a routed
  * mixture-of-experts FFN (App. B, MoE configurations), whose routed rows are
  * stored expert-major so that group e owns rows [offsets[e], offsets[e+1]).
@@ -563,6 +585,11 @@ forge_status forge_gemm_grouped_rows(int32_t layout_b, const forge_bf16* A, cons
                                      int32_t rows, int32_t N, int32_t K, int64_t lda,
                                      int64_t ldb, int64_t ldc, int64_t stride_b,
                                      forge_stream stream);
+
+/* Host only: the output tile of forge_gemm_grouped_rows at these sizes. */
+forge_status forge_gemm_grouped_rows_tile(int32_t layout_b, int32_t groups, int32_t rows,
+                                          int32_t N, int32_t K, int32_t* tile_m,
+                                          int32_t* tile_n);
 
 /*
  * forge_gemm_grouped_wgrad: the per-expert weight gradients, for each group e

@@ -146,6 +146,14 @@ def load():
         "forge_clip_coeff": (ctypes.c_int, [P, F32, F32, P, P]),
         "forge_gemm": (ctypes.c_int, [I32, I32, I32, P, P, P, P, I32, I32, I32,
                                       I64, I64, I64, I64, P]),
+        "forge_gemm_scratch": (ctypes.c_int, [I32, I32, I32, P, P, P, P, I32, I32, I32,
+                                              I64, I64, I64, I64, F32, P, ctypes.c_size_t, P]),
+        "forge_gemm_plan": (ctypes.c_int, [I32, I32, I32, I32, I32, ctypes.c_size_t,
+                                           ctypes.POINTER(I32), ctypes.POINTER(I32),
+                                           ctypes.POINTER(I32), SZ]),
+        "forge_gemm_grouped_rows_tile": (ctypes.c_int, [I32, I32, I32, I32, I32,
+                                                        ctypes.POINTER(I32),
+                                                        ctypes.POINTER(I32)]),
         "forge_gemm_grouped_rows": (ctypes.c_int, [I32, P, P, P, P, I32, I32, I32, I32,
                                                    I64, I64, I64, I64, P]),
         "forge_gemm_grouped_wgrad": (ctypes.c_int, [P, P, P, P, I32, I32, I32, I64, I64,
@@ -384,6 +392,28 @@ def forge_gemm(layout_a, layout_b, epilogue, A, B, C, R, M, N, K, lda, ldb, ldc,
                stream=None):
     _check(load().forge_gemm(layout_a, layout_b, epilogue, _ptr(A), _ptr(B), _ptr(C),
                              _ptr(R), M, N, K, lda, ldb, ldc, ldr, _stream(stream)))
+
+
+def forge_gemm_scratch(layout_a, layout_b, epilogue, A, B, C, R, M, N, K, lda, ldb, ldc, ldr,
+                       alpha, scratch, scratch_bytes, stream=None):
+    _check(load().forge_gemm_scratch(layout_a, layout_b, epilogue, _ptr(A), _ptr(B), _ptr(C),
+                                     _ptr(R), M, N, K, lda, ldb, ldc, ldr, alpha, _ptr(scratch),
+                                     scratch_bytes, _stream(stream)))
+
+
+def forge_gemm_plan(layout_a, layout_b, M, N, K, scratch_bytes=0):
+    """(tile_m, tile_n, splits, scratch bytes taken) of a product."""
+    tm, tn, s, n = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32(), ctypes.c_size_t()
+    _check(load().forge_gemm_plan(layout_a, layout_b, M, N, K, scratch_bytes, ctypes.byref(tm),
+                                  ctypes.byref(tn), ctypes.byref(s), ctypes.byref(n)))
+    return tm.value, tn.value, s.value, n.value
+
+
+def forge_gemm_grouped_rows_tile(layout_b, groups, rows, N, K):
+    tm, tn = ctypes.c_int32(), ctypes.c_int32()
+    _check(load().forge_gemm_grouped_rows_tile(layout_b, groups, rows, N, K, ctypes.byref(tm),
+                                               ctypes.byref(tn)))
+    return tm.value, tn.value
 
 
 def forge_gemm_grouped_rows(layout_b, A, B, C, offsets, groups, rows, N, K, lda, ldb, ldc,

@@ -1535,10 +1535,30 @@ forge_status forge_clip_coeff(const float* norm_sq, float max_norm, float eps,
 }
 
 // ---- building blocks --------------------------------------------------------
+namespace {
+forge_status check_gemm_sizes(int32_t layout_a, int32_t layout_b, int32_t M, int32_t N, int32_t K) {
+  FORGE_CHECK(M >= 0 && N >= 0 && K >= 0, FORGE_ERR_INVALID_ARG, "negative size");
+  FORGE_CHECK(layout_a == 1 || K % 8 == 0, FORGE_ERR_INVALID_ARG, "K-contiguous A needs K %% 8 == 0");
+  FORGE_CHECK(layout_b == 1 || K % 8 == 0, FORGE_ERR_INVALID_ARG, "K-contiguous B needs K %% 8 == 0");
+  FORGE_CHECK(layout_a == 0 || M % 8 == 0, FORGE_ERR_INVALID_ARG, "M-contiguous A needs M %% 8 == 0");
+  FORGE_CHECK(layout_b == 0 || N % 8 == 0, FORGE_ERR_INVALID_ARG, "N-contiguous B needs N %% 8 == 0");
+  return FORGE_OK;
+}
+}  // namespace
+
 forge_status forge_gemm(int32_t layout_a, int32_t layout_b, int32_t epilogue,
                         const forge_bf16* A, const forge_bf16* B, void* C, const forge_bf16* R,
                         int32_t M, int32_t N, int32_t K, int64_t lda, int64_t ldb, int64_t ldc,
                         int64_t ldr, forge_stream stream) {
+  return forge_gemm_scratch(layout_a, layout_b, epilogue, A, B, C, R, M, N, K, lda, ldb, ldc, ldr,
+                            1.0f, nullptr, 0, stream);
+}
+
+forge_status forge_gemm_scratch(int32_t layout_a, int32_t layout_b, int32_t epilogue,
+                                const forge_bf16* A, const forge_bf16* B, void* C,
+                                const forge_bf16* R, int32_t M, int32_t N, int32_t K, int64_t lda,
+                                int64_t ldb, int64_t ldc, int64_t ldr, float alpha, void* scratch,
+                                size_t scratch_bytes, forge_stream stream) {
   FORGE_CHECK((layout_a == 0 || layout_a == 1) && (layout_b == 0 || layout_b == 1) &&
                   epilogue >= 0 && epilogue <= 3,
               FORGE_ERR_INVALID_ARG, "bad layout or epilogue code");
@@ -1555,10 +1575,10 @@ forge_status forge_gemm(int32_t layout_a, int32_t layout_b, int32_t epilogue,
     FORGE_PTR(A);
     FORGE_PTR(B);
   }
-  FORGE_CHECK(layout_a == 1 || K % 8 == 0, FORGE_ERR_INVALID_ARG, "K-contiguous A needs K %% 8 == 0");
-  FORGE_CHECK(layout_b == 1 || K % 8 == 0, FORGE_ERR_INVALID_ARG, "K-contiguous B needs K %% 8 == 0");
-  FORGE_CHECK(layout_a == 0 || M % 8 == 0, FORGE_ERR_INVALID_ARG, "M-contiguous A needs M %% 8 == 0");
-  FORGE_CHECK(layout_b == 0 || N % 8 == 0, FORGE_ERR_INVALID_ARG, "N-contiguous B needs N %% 8 == 0");
+  if (forge_status e = check_gemm_sizes(layout_a, layout_b, M, N, K)) return e;
+  FORGE_CHECK(std::isfinite(alpha), FORGE_ERR_INVALID_ARG, "alpha must be finite");
+  FORGE_CHECK(scratch != nullptr || scratch_bytes == 0, FORGE_ERR_INVALID_ARG, "scratch is NULL");
+  FORGE_CHECK(aligned16(scratch), FORGE_ERR_ALIGNMENT, "scratch is not 16-byte aligned");
   FORGE_CHECK(lda % 8 == 0 && ldb % 8 == 0 && ldc % 8 == 0, FORGE_ERR_INVALID_ARG,
               "leading dimensions must be multiples of 8");
   FORGE_CHECK(lda >= (layout_a == 0 ? K : M) && ldb >= (layout_b == 0 ? K : N) && ldc >= N,
@@ -1573,9 +1593,27 @@ forge_status forge_gemm(int32_t layout_a, int32_t layout_b, int32_t epilogue,
     FORGE_CHECK(c1 <= r0 || r1 <= c0, FORGE_ERR_INVALID_ARG, "R overlaps C");
   }
   FORGE_CHECK((int64_t)M * ldc < (1LL << 40), FORGE_ERR_INVALID_ARG, "C too large");
-  GemmArgs g = gargs(A, lda, B, ldb, C, ldc, M, N, K, R, ldr);
   FORGE_HIP(forge::gemm((forge::GemmLayout)layout_a, (forge::GemmLayout)layout_b,
-                        (forge::GemmEpilogue)epilogue, g, (hipStream_t)stream));
+                        (forge::GemmEpilogue)epilogue,
+                        scaled(gargs(A, lda, B, ldb, C, ldc, M, N, K, R, ldr), alpha),
+                        (hipStream_t)stream, static_cast<float*>(scratch), scratch_bytes));
+  return ok();
+}
+
+forge_status forge_gemm_plan(int32_t layout_a, int32_t layout_b, int32_t M, int32_t N, int32_t K,
+                             size_t scratch_bytes, int32_t* tile_m, int32_t* tile_n,
+                             int32_t* splits, size_t* bytes) {
+  FORGE_CHECK((layout_a == 0 && (layout_b == 0 || layout_b == 1)) ||
+                  (layout_a == 1 && layout_b == 1),
+              FORGE_ERR_UNSUPPORTED, "layout combination (%d,%d)", layout_a, layout_b);
+  if (forge_status e = check_gemm_sizes(layout_a, layout_b, M, N, K)) return e;
+  FORGE_CHECK(M > 0 && N > 0, FORGE_ERR_INVALID_ARG, "an empty product has no plan");
+  const forge::GemmPlan p = forge::gemm_plan((forge::GemmLayout)layout_a,
+                                             (forge::GemmLayout)layout_b, M, N, K, scratch_bytes);
+  if (tile_m) *tile_m = p.tile_m;
+  if (tile_n) *tile_n = p.tile_n;
+  if (splits) *splits = p.splits;
+  if (bytes) *bytes = p.bytes;
   return ok();
 }
 
@@ -1607,6 +1645,20 @@ forge_status forge_gemm_grouped_rows(int32_t layout_b, const forge_bf16* A, cons
   GemmArgs g = grouped(gargs(A, lda, B, ldb, C, ldc, rows, N, K), offsets, groups, stride_b, 0);
   FORGE_HIP(forge::gemm_grouped_m((forge::GemmLayout)layout_b, forge::kStoreBF16, g,
                                   (hipStream_t)stream));
+  return ok();
+}
+
+forge_status forge_gemm_grouped_rows_tile(int32_t layout_b, int32_t groups, int32_t rows,
+                                          int32_t N, int32_t K, int32_t* tile_m,
+                                          int32_t* tile_n) {
+  FORGE_CHECK(layout_b == FORGE_GEMM_KC || layout_b == FORGE_GEMM_MC, FORGE_ERR_INVALID_ARG,
+              "bad layout_b");
+  FORGE_CHECK(groups > 0 && rows > 0 && N > 0 && K >= 0, FORGE_ERR_INVALID_ARG, "bad size");
+  FORGE_CHECK(tile_m != nullptr && tile_n != nullptr, FORGE_ERR_INVALID_ARG, "NULL pointer");
+  const forge::GemmPlan p =
+      forge::gemm_grouped_m_plan((forge::GemmLayout)layout_b, rows, groups, N, K);
+  *tile_m = p.tile_m;
+  *tile_n = p.tile_n;
   return ok();
 }
 

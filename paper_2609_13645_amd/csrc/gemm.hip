@@ -1316,9 +1316,18 @@ hipError_t gemm_grouped_k(GemmEpilogue epi, const GemmArgs& a, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
+GemmPlan gemm_plan(GemmLayout la, GemmLayout lb, long M, long N, long K, size_t part_bytes) {
+  const Plan pl = pick_plan(layout_id(la, lb), M, N, K, part_bytes);
+  return {kTileM[pl.tile], kTileN[pl.tile], pl.splits, partial_bytes(pl.splits, M, N)};
+}
+
+GemmPlan gemm_grouped_m_plan(GemmLayout lb, long rows, long groups, long N, long K) {
+  const Tile t = pick_grouped_tile(layout_id(kKC, lb), rows, groups, N, K);
+  return {kTileM[t], kTileN[t], 1, 0};
+}
+
 size_t gemm_split_bytes(GemmLayout la, GemmLayout lb, long M, long N, long K) {
-  if (M <= 0 || N <= 0) return 0;
-  return partial_bytes(pick_plan(layout_id(la, lb), M, N, K, SIZE_MAX).splits, M, N);
+  return M <= 0 || N <= 0 ? 0 : gemm_plan(la, lb, M, N, K, SIZE_MAX).bytes;
 }
 
 hipError_t gemm(GemmLayout la, GemmLayout lb, GemmEpilogue epi, const GemmArgs& a, hipStream_t s,

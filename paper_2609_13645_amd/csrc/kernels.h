@@ -62,6 +62,13 @@ struct GemmArgs {
 // partials added in a fixed order; gemm_split_bytes is what the product would
 // use (0: it does not split). With less scratch it splits into fewer parts.
 size_t gemm_split_bytes(GemmLayout la, GemmLayout lb, long M, long N, long K);
+// How a product runs, and the tile of one over row groups (host only).
+struct GemmPlan {
+  int tile_m, tile_n, splits;
+  size_t bytes;  // of partial products
+};
+GemmPlan gemm_plan(GemmLayout la, GemmLayout lb, long M, long N, long K, size_t part_bytes);
+GemmPlan gemm_grouped_m_plan(GemmLayout lb, long rows, long groups, long N, long K);
 hipError_t gemm(GemmLayout la, GemmLayout lb, GemmEpilogue epi, const GemmArgs& a,
                 hipStream_t stream, float* part = nullptr, size_t part_bytes = 0);
 // Grouped forms, one product per group e with rows [g_off[e], g_off[e+1]):

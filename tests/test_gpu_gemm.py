@@ -148,17 +148,73 @@ def test_gemm_split_last_round_integer_exact(M, N, K, epi):
 
 # below a chip full of 256 x 256 tiles: 64 x 64 with the reduction split over
 # the waves (fewer stages than waves, one ragged stage, ragged tiles in both
-# directions), 128 x 128, 128 x 256, 256 x 256
+# directions), 128 x 128, 128 x 256, 256 x 256; test_gemm_plan.py checks that
+# each layout has all four
+TILE_SIZES = [(64, 64, 32), (72, 56, 104), (1000, 264, 2056), (2056, 1032, 296), (3080, 1032, 1000),
+              (2056, 2040, 2072), (2824, 2704, 904), (3840, 4088, 1032),
+              (5000, 1000, 520)]   # 320 tiles of 128 x 128: a partly shared round
+
+
 @pytest.mark.parametrize("la,lb,epi", COMBOS)
-@pytest.mark.parametrize("M,N,K", [(64, 64, 32), (72, 56, 104), (1000, 264, 2056), (2056, 1032, 296),
-                                   (3080, 1032, 1000), (2056, 2040, 2072), (3840, 4088, 1032),
-                                   (5000, 1000, 520)])   # 320 tiles of 128 x 128: a partly shared round
+@pytest.mark.parametrize("M,N,K", TILE_SIZES)
 def test_gemm_tile_choice_integer_exact(la, lb, epi, M, N, K):
     banner(f"gemm int tile choice la={la} lb={lb} epi={epi} M={M} N={N} K={K}")
     got, ref = run_gemm(la, lb, epi, M, N, K, seed=M + N + K + epi)
     want = (fi.bf16_bits_to_f64(fi.to_bf16_bits(ref.astype(np.float32)))
             if epi in (STORE_BF16, RESID_BF16) else ref)
     assert np.array_equal(got, want)
+
+
+# layouts, sizes, tile and splits of products whose reduction is split over
+# workgroups: ragged tiles in both directions, a shorter last split, odd M and N
+# (N % 8 != 0) where the layouts take them
+SPLITS = [(KC, KC, 77, 203, 2408, (64, 64), 13), (KC, KC, 645, 451, 5544, (128, 128), 8),
+          (KC, KC, 1285, 907, 5360, (128, 256), 5), (KC, KC, 2709, 843, 7992, (256, 256), 5),
+          (KC, MC, 77, 200, 1800, (64, 64), 10), (KC, MC, 1109, 968, 2120, (128, 128), 3),
+          (KC, MC, 1325, 912, 2504, (128, 256), 4), (KC, MC, 2181, 1040, 8384, (256, 256), 5),
+          (MC, MC, 72, 200, 2016, (64, 64), 11), (MC, MC, 1224, 72, 2368, (128, 128), 13),
+          (MC, MC, 1424, 1296, 3736, (128, 256), 3), (MC, MC, 2752, 808, 7904, (256, 256), 5)]
+
+
+@pytest.mark.parametrize("la,lb,M,N,K,tile,splits,epi", [
+    s + (epi,) for s in SPLITS for la, lb, epi in COMBOS if (la, lb) == s[:2]])
+def test_gemm_split_integer_exact(la, lb, M, N, K, tile, splits, epi):
+    """Every split tile and epilogue, scaled by 1/2: exact, whatever the scratch
+    held before, and nothing written past the scratch or beside C; with less
+    scratch fewer splits and the same values."""
+    import torch
+    from paper_2609_13645_amd import _lib
+    banner(f"gemm int split la={la} lb={lb} M={M} N={N} K={K} epi={epi}")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K + epi)
+
+    def ints(shape, hi):
+        return torch.randint(-hi, hi + 1, shape, generator=gen, device="cuda").float()
+
+    A, B = ints((M, K) if la == KC else (K, M), 4), ints((N, K) if lb == KC else (K, N), 4)
+    ld = (N + 7) // 8 * 8 + 8
+    R, init = ints((M, ld), 8), ints((M, ld), 8)
+    # half of a sum of at most 16 K < 2^18: exact in fp32
+    ref = 0.5 * ((A if la == KC else A.T) @ (B.T if lb == KC else B))
+    bf = epi in (STORE_BF16, RESID_BF16)
+    if epi == RESID_BF16:
+        ref += R[:, :N]
+    if epi == ACC_F32:
+        ref += init[:, :N]
+    ref = ref.bfloat16() if bf else ref
+    *got, need = _lib.forge_gemm_plan(la, lb, M, N, K, 1 << 40)
+    assert (tuple(got[:2]), got[2]) == (tile, splits)
+    for room in (need, need // 2):
+        C = init.bfloat16() if bf else init.clone()
+        scratch = torch.full((need // 4 + 64,), float("nan"), device="cuda")
+        scratch[room // 4:] = 7.0
+        _lib.forge_gemm_scratch(la, lb, epi, A.bfloat16(), B.bfloat16(), C,
+                                R.bfloat16() if epi == RESID_BF16 else None, M, N, K, A.shape[1],
+                                B.shape[1], ld, ld if epi == RESID_BF16 else 0, 0.5, scratch, room)
+        torch.cuda.synchronize()
+        assert torch.equal(C[:, :N], ref)
+        assert torch.equal(C[:, N:].float(), init[:, N:])
+        assert bool((scratch[room // 4:] == 7.0).all())
 
 
 @pytest.mark.parametrize("M,N,K", [(100, 77, 72), (129, 1031, 520)])
@@ -244,22 +300,25 @@ def test_gemm_256x192_tiles_integer_exact(epi):
 
 
 GROUP_SIZES = [0, 37, 256, 1, 300, 0, 129, 8, 513]
+LARGE_GROUPS = [0, 700, 1, 1300, 0, 513, 256, 1030]
+GROUPED = [(GROUP_SIZES, 136, 64, (64, 64)), (GROUP_SIZES, 264, 200, (64, 64)),
+           (GROUP_SIZES, 3080, 1000, (128, 256)), (LARGE_GROUPS, 2056, 264, (256, 256))]
 
 
 @pytest.mark.parametrize("lb", [KC, MC])
-# few tiles (64 x 64 at the first two sizes), 128 x 256 tiles
-@pytest.mark.parametrize("N,K", [(136, 64), (264, 200), (3080, 1000)])
-def test_grouped_rows_integer_exact(lb, N, K):
+@pytest.mark.parametrize("sizes,N,K,tile", GROUPED)
+def test_grouped_rows_integer_exact(lb, sizes, N, K, tile):
     """Per-group products over expert-major rows, ragged and empty groups;
     rows past the last offset are never written."""
     import torch
     from paper_2609_13645_amd import _lib
     banner(f"grouped rows lb={lb} N={N} K={K}")
     rng = np.random.default_rng(N + K + lb)
-    off = np.concatenate([[0], np.cumsum(GROUP_SIZES)]).astype(np.int32)
-    G, rows = len(GROUP_SIZES), int(off[-1]) + 40          # a slack of unused rows
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    G, rows = len(sizes), int(off[-1]) + 40          # a slack of unused rows
     A = rng.integers(-4, 5, size=(rows, K)).astype(np.float32)
     B = rng.integers(-4, 5, size=(G, N, K) if lb == KC else (G, K, N)).astype(np.float32)
+    assert _lib.forge_gemm_grouped_rows_tile(lb, G, rows, N, K) == tile
     C = torch.full((rows, N), float("nan"), dtype=torch.bfloat16, device="cuda")
     _lib.forge_gemm_grouped_rows(lb, dev_bf16(fi.to_bf16_bits(A)), dev_bf16(fi.to_bf16_bits(B)),
                                  C, torch.from_numpy(off).cuda(), G, rows, N, K, K,
