@@ -1087,11 +1087,17 @@ constexpr int kCUs = 256;
 // CU at most one of them costs `half`; one that gives some two costs a whole one,
 // except with both operands K-contiguous at 128 x 128, whose kernel's cost rises
 // evenly: with K 4096 45 us at 256 tiles, 50 at 288, 53 at 320, 60 at 384,
-// and 51, 52, 54, 57 on 128 x 256). The constants are a fit (10-15 % rms)
+// and 51, 52, 54, 57 on 128 x 256. Over products of 257 to 511 tiles of 128 x 128
+// the picks are 3.5 % from the fastest tile with the even rise and 3.7 % without
+// (120 products, 6 of them then slower than one 256 x 128 launch); in the data
+// gradient 11 % with it and 0.2 % without (20), in the weight gradient 9.8 and
+// 6.6 % (72)). The constants are a fit (10-15 % rms)
 // to 130 products, M, N in 64..16384, K in 64..16384, all layouts, timed on
 // every tile: the pick is on average 2 % slower than the fastest tile, and
 // 1.47 times as fast as one threshold on the number of tiles (256 x 256 from
-// 256 tiles, then 256 x 128, else 128 x 128). E.g. (M, N, K) = (1000, 1024,
+// 256 tiles, then 256 x 128, else 128 x 128). The round of 64 x 64 tiles is set by
+// reductions below 320 (1792 x 1800 x 40, data gradient, 841 tiles: 10.8 us, 8.3 on
+// 128 x 128). E.g. (M, N, K) = (1000, 1024,
 // 3072), data gradient: 12.7 us on 64 x 64, 40.7 on 128 x 128; (2048, 2048,
 // 3072): 38 on 128 x 256, 41 on 128 x 128, 60 on 256 x 256.
 enum Tile { kT256, kT128x256, kT128, kT64, kTiles };
@@ -1100,7 +1106,7 @@ struct TileCost {
   double fixed, per_k, full_k;
 };
 constexpr int kSlots[kTiles] = {256, 256, 512, 512};
-constexpr double kHalfRound[kTiles] = {1.0, 1.0, 0.55, 0.52}, kRound[kTiles] = {8.0, 5.0, 6.0, 1.7};
+constexpr double kHalfRound[kTiles] = {1.0, 1.0, 0.55, 0.52}, kRound[kTiles] = {8.0, 5.0, 6.0, 2.5};
 // [layout: (KC, KC), (KC, MC), (MC, MC)][tile]
 constexpr TileCost kCost[3][kTiles] = {
     {{10.0, .0150, .0120}, {6.0, .0092, .0068}, {4.3, .0110, .0070}, {3.7, .0037, .0040}},
@@ -1151,9 +1157,14 @@ size_t partial_bytes(int S, long M, long N) {
 // scratch: bytes there are for partial tiles
 Plan pick_plan(int layout, long M, long N, long K, size_t scratch) {
   Plan best = {kT256, 1, K};
-  // from a chip full of 256 x 256 tiles up no other tile is faster (8192 x
-  // 1536 x 1536 has 192: 36.9 us, 128 x 128 46.8, 128 x 256 50.1)
-  if (tile_count(kT256, M, N) >= kCUs) return best;
+  // From a chip of well filled 256 x 256 tiles up no other tile is better on
+  // average (192 to 640 rows or columns: 0.84 to 1.5 times the estimate's pick;
+  // 8192 x 1536 x 1536 has 192 tiles: 36.9 us, 128 x 128 46.8, 128 x 256 50.1).
+  // With M or N of at most 128, or just above 256, half of each tile and more is
+  // padding: 64 x 75072 x 368, data gradient, 24.2 us, 17.0 on the pick; 264 x
+  // 98624 x 432 59 and 46; at 136 and 9/16 filled the two are level.
+  const long big = tile_count(kT256, M, N);
+  if (big >= kCUs && (double)M * (double)N > big * (65536.0 * 9 / 16)) return best;
   double cost = 1e30;
   for (int t = 0; t < kTiles; ++t) {
     const long tiles = tile_count(t, M, N);

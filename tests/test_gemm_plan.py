@@ -18,6 +18,22 @@ def test_gpu_sizes_reach_every_tile(la, lb):
     assert {_lib.forge_gemm_plan(la, lb, *s)[:2] for s in g.TILE_SIZES} == TILES
 
 
+@pytest.mark.parametrize("la,lb", LAYOUTS)
+def test_padding_counts_against_large_tiles(la, lb):
+    """A chip of 256 x 256 tiles that are mostly padding is no reason to take
+    them: no jump where their number reaches the CUs'."""
+    for M, N in ((64, 65280), (64, 65536), (65536, 64), (8, 100000), (128, 131072)):
+        assert _lib.forge_gemm_plan(la, lb, M, N, 2048)[:2] != (256, 256), (M, N)
+    for M, N in ((4096, 4096), (4000, 4008), (192, 131072), (16384, 1024)):
+        assert _lib.forge_gemm_plan(la, lb, M, N, 2048)[:2] == (256, 256), (M, N)
+
+
+def test_short_reductions_on_many_small_tiles():
+    # data gradients of 40 to 200: more than a round of 64 x 64 tiles
+    for M, N, K in ((1792, 1800, 40), (2016, 1480, 72), (3056, 1120, 72), (328, 7520, 184)):
+        assert _lib.forge_gemm_plan(0, 1, M, N, K)[:2] == (128, 128), (M, N, K)
+
+
 @pytest.mark.parametrize("la,lb,M,N,K,tile,splits", g.SPLITS)
 def test_gpu_split_sizes_split_as_they_say(la, lb, M, N, K, tile, splits):
     tm, tn, s, n = _lib.forge_gemm_plan(la, lb, M, N, K, PLENTY)
