@@ -47,6 +47,7 @@
 //  * Workgroups are dispatched round-robin over the 8 XCDs; the tile order is
 //    remapped so each XCD works on a contiguous, M-grouped band of tiles and
 //    reuses operands in its own L2.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -1166,15 +1167,28 @@ Plan pick_plan(int layout, long M, long N, long K, size_t scratch) {
   const long big = tile_count(kT256, M, N);
   if (big >= kCUs && (double)M * (double)N > big * (65536.0 * 9 / 16)) return best;
   double cost = 1e30;
+  long tiles[kTiles];
   for (int t = 0; t < kTiles; ++t) {
-    const long tiles = tile_count(t, M, N);
-    for (int S = 1; S <= kMaxSplit; ++S) {
-      if (tiles * S > kCUs && S > 1) break;
-      if (K < (long)S * kMinSplitK && S > 1) break;
-      if (partial_bytes(S, M, N) > scratch) break;
-      const long ks = S > 1 ? split_len(K, S) : K;
-      if (S > 1 && (K + ks - 1) / ks != S) continue;  // the last split would be empty
-      const double c = tile_cost(layout, t, tiles * S, ks) + (S > 1 ? reduce_cost(S, M, N) : 0.0);
+    tiles[t] = t == kT256 ? big : tile_count(t, M, N);
+    const double c = tile_cost(layout, t, tiles[t], K);
+    if (c < cost) {
+      cost = c;
+      best = {(Tile)t, 1, K};
+    }
+  }
+  for (int t = 0; t < kTiles; ++t) {
+    const int most = (int)std::min<long>(std::min<long>(kMaxSplit, kCUs / tiles[t]), K / kMinSplitK);
+    const TileCost& tc = kCost[layout][t];
+    for (int S = 2; S <= most; ++S) {
+      // Partials of S splits alone, and of more, cost too much; or with a round of
+      // the shorter reduction. (A layer call plans each of its products twice: a
+      // small layer's take 0.6 us instead of 1.9.)
+      const double extra = reduce_cost(S, M, N);
+      if (tc.fixed + extra >= cost || partial_bytes(S, M, N) > scratch) break;
+      if (tc.fixed + extra + (double)(K / S) * tc.per_k * 0.5 >= cost) continue;
+      const long ks = split_len(K, S);
+      if ((K + ks - 1) / ks != S) continue;  // the last split would be empty
+      const double c = tile_cost(layout, t, tiles[t] * S, ks) + extra;
       if (c < cost) {
         cost = c;
         best = {(Tile)t, S, ks};
