@@ -95,22 +95,15 @@ def kc_kernel_name(M, N, suffix):
     """Kernel(s) and tile the library's dispatch picks for a plain GEMM with
     both operands K-contiguous (for labelling the roofline kernel only): full
     256 x 256 tiles on the ring pipeline, with a last round at most half full
-    run as 256 x 128 halves in a second launch; 256 x 192 when that fills the
-    last wave of workgroups better; below a chip of 256 x 256 tiles the
-    library's cost estimate picks the tile (and splits), which is not repeated
-    here. `suffix` closes each template argument list."""
+    run as 256 x 128 halves in a second launch; below a chip of well filled
+    256 x 256 tiles the library's cost estimate picks the tile (and splits),
+    which is not repeated here. `suffix` closes each template argument list."""
     big = -(-M // 256) * -(-N // 256)
-    if big >= 256:
-        tail = big % 256
-        if big > 256 and 0 < tail <= 128:
-            return f"ring_kernel<256,256,2,4{suffix} + ring_kernel<256,128,2,4{suffix}"
-        t192 = -(-M // 256) * -(-N // 192)
-        c256 = -(-big // 256) * 256.0
-        c192 = -(-t192 // 256) * 192.0 / 0.74
-        head = "gemm_kernel<256,192,4,2" if c192 < c256 else "ring_kernel<256,256,2,4"
-    else:
+    if big < 256 or M * N <= big * 65536 * 9 // 16:
         return "ring_kernel / wave_kernel (tile by estimated cost)"
-    return head + suffix
+    if big > 256 and 0 < big % 256 <= 128:
+        return f"ring_kernel<256,256,2,4{suffix} + ring_kernel<256,128,2,4{suffix}"
+    return f"ring_kernel<256,256,2,4{suffix}"
 
 
 class Step:

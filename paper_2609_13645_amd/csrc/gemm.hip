@@ -20,7 +20,7 @@
 //    which keeps the clock higher under load.
 //  * wave_kernel (every layout; 64 x 64 tiles, for products of few tiles): the
 //    waves of a workgroup split the reduction, each with a ring of its own.
-//  * gemm_kernel (K-contiguous 256 x 192 and 128 x 128): v_mfma_f32_32x32x16
+//  * gemm_kernel (K-contiguous 128 x 128): v_mfma_f32_32x32x16
 //    over a block tile BM x BN x 64 double-buffered in LDS, one barrier per
 //    k-step placed before the step's last 16-deep slice; the barrier also
 //    frees the current buffer, which is refilled at once with the step after
@@ -1007,12 +1007,11 @@ __global__ __launch_bounds__(NW * 64) void wave_kernel(GemmArgs p) {
   }
 }
 
-// The ring pipeline runs every tile except the K-contiguous 256 x 192 and
-// 128 x 128 ones, which run on the double-buffered kernel.
+// The ring pipeline runs every tile except the K-contiguous 128 x 128 one, which
+// runs on the double-buffered kernel.
 template <int BM, int BN, int WAVES_M, int WAVES_N, int LA, int LB, int EPI, int GROUP>
 void launch_kernel(const GemmArgs& a, long grid, hipStream_t s) {
-  constexpr bool kBuffered = LA == kKC && LB == kKC && GROUP == 0 &&
-                             ((BM == 256 && BN == 192) || (BM == 128 && BN == 128));
+  constexpr bool kBuffered = LA == kKC && LB == kKC && GROUP == 0 && BM == 128 && BN == 128;
   if constexpr (kBuffered)
     hipLaunchKernelGGL((gemm_kernel<BM, BN, WAVES_M, WAVES_N, LA, LB, EPI, GROUP>),
                        dim3((unsigned)grid), dim3(WAVES_M * WAVES_N * 64), 0, s, a);
@@ -1254,17 +1253,6 @@ hipError_t dispatch_tiles(const GemmArgs& a, hipStream_t s, float* part, size_t 
       launch_kernel<256, 128, 2, 4, LA, LB, EPI, 4>(b, 2 * tail, s);
       return hipGetLastError();
     }
-    if (big >= kCUs) {
-      // 256 x 192 tiles when 256 x 256 ones leave the last wave of workgroups
-      // partly empty: cost ~ waves x tile area, the narrower (double-buffered)
-      // tile being ~26 % less efficient per FLOP than the ring's 256 x 256
-      // (measured on the 4096 x 6144 x 4096 product: two rounds of each,
-      // 200 us on the ring against 208-212 us)
-      const long t192 = (long)((a.M + 255) / 256) * ((a.N + 191) / 192);
-      const double c256 = (double)((big + kCUs - 1) / kCUs) * 256.0;
-      const double c192 = (double)((t192 + kCUs - 1) / kCUs) * 192.0 / 0.74;
-      if (c192 < c256) return launch<256, 192, 4, 2, LA, LB, EPI>(a, s);
-    }
   }
   // 128 x 64 wave tiles (2 x 4 waves, two per SIMD): in a data gradient (B
   // M/N-contiguous, read with the slower transposing reads) they put the
@@ -1314,8 +1302,8 @@ hipError_t launch_grouped_rows(const GemmArgs& a, hipStream_t s) {
   }
   // the transposing reads of an M/N-contiguous weight on the narrow side of
   // the wave tile (128 x 64 waves), as in the ungrouped data gradient
-  return LB == kKC ? launch_grouped_m<256, 256, 4, 2, LB, kStoreBF16>(a, s)
-                   : launch_grouped_m<256, 256, 2, 4, LB, kStoreBF16>(a, s);
+  if constexpr (LB == kKC) return launch_grouped_m<256, 256, 4, 2, LB, kStoreBF16>(a, s);
+  else return launch_grouped_m<256, 256, 2, 4, LB, kStoreBF16>(a, s);
 }
 
 }  // namespace

@@ -287,12 +287,11 @@ def test_gemm_zero_k_and_empty():
 
 
 @pytest.mark.parametrize("epi", [STORE_BF16, RESID_BF16, ACC_F32, STORE_F32])
-def test_gemm_256x192_tiles_integer_exact(epi):
-    """A K-contiguous product whose 256 x 256 tiles would leave the last wave
-    of workgroups half empty runs on 256 x 192 tiles; N = 6136 also leaves a
-    ragged last tile column."""
+def test_gemm_half_round_ragged_columns_integer_exact(epi):
+    """A K-contiguous product whose 256 x 256 tiles leave half a round, a single
+    ragged stage of K and, with N = 6136, a ragged last tile column."""
     M, N, K = 4096, 6136, 40
-    banner(f"gemm 256x192 tiles epi={epi}")
+    banner(f"gemm half round ragged columns epi={epi}")
     got, ref = run_gemm(KC, KC, epi, M, N, K, seed=epi + 11)
     want = (fi.bf16_bits_to_f64(fi.to_bf16_bits(ref.astype(np.float32)))
             if epi in (STORE_BF16, RESID_BF16) else ref)
