@@ -486,7 +486,8 @@ typedef struct {
  * is in flight (layers of fewer than 2^20 token x hidden elements, where
  * the stream hand-offs would cost more than they save, and of 2^26 and more,
  * whose products fill the chip by themselves, run the updates in order on
- * `stream`).
+ * `stream`; routed layers of 2^26 and more only where their expert weight
+ * gradients have at least 2560 tiles of 256 x 256).
  * opt: each used entry's param must be the same pointer as the matching
  *   member of w (the update overwrites the weight in place, after the
  *   backward's last read of it); master, m, v are updated in place.

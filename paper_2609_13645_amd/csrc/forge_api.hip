@@ -443,9 +443,9 @@ forge_status attn_block_fwd(const forge_layer_cfg& c, const Dims& d,
 }
 
 // ---- side streams of the layer backward ----------------------------------------
-// The dense layer backward (from 2^20 to 2^26 token x hidden elements) runs its
-// four weight-gradient GEMMs on a second stream of the same device, forked from the caller's stream after each one's
-// inputs exist and joined back before the call's work ends, so they fill the
+// The layer backward (where use_side_streams says so) runs its weight-gradient
+// GEMMs on a second stream of the same device, forked from the caller's stream after
+// each one's inputs exist and joined back before the call's work ends, so they fill the
 // tail waves of the data-gradient GEMMs and the bandwidth-bound kernels in
 // between. forge_layer_bwd_adamw adds a third stream for the optimizer
 // updates, each forked once its weight's gradient is complete and its
@@ -469,14 +469,23 @@ std::mutex g_side_init;
 
 // Side streams only for layers whose products outlast the event hand-offs (2048
 // tokens x 2048: 943 us with them, 1005 without) and up to 2^26 token x hidden
-// elements. From there on every product fills the chip for many rounds, so
-// nothing is left to fill, and products sharing it only take each other's cache:
-// dense, 4 x 4096 tokens x 4096, 21.8 ms with them and 21.1 without (with AdamW
-// 22.8 and 22.1; one 16384-token sequence 28.2 and 27.5); 64 experts, 8 x 4096 x
-// 2048, 21.2 and 20.9. At half that size either way: 8192 x 4096, 10.63 and 10.50
-// ms, with AdamW 11.57 and 11.65; 16384 x 2048, 6.21 and 6.20.
+// elements. From there on every product of a dense layer fills the chip for many
+// rounds (or splits its reduction until it does), so nothing is left to fill, and
+// products sharing it only take each other's cache: 4 x 4096 tokens x 4096, 21.8
+// ms with them and 21.1 without (with AdamW 22.9 and 22.2; one 16384-token sequence
+// 28.2 and 27.5), 8 x 4096 x 2048 14.8 and 14.5, level at hidden 256 to 1024. At half
+// that size either way: 8192 x 4096, 10.63 and 10.50 ms, with AdamW 11.57 and 11.65;
+// 16384 x 2048, 6.21 and 6.20. The expert weight gradients of a routed layer do not
+// split: they fill the chip only with ten rounds of 256 x 256 tiles or more (64
+// experts of 1408, 8 x 4096 x 2048: 5632 tiles, 21.5 ms with side streams and 21.4
+// without, with AdamW 23.5 and 23.1; 8 of 5632: 2816 tiles, 20.4 and 20.3). With fewer
+// the side stream still fills their last rounds: 8 experts of 1408, 32768 x 2048, 704
+// tiles, 9.04 and 9.37; 65536 x 1024, 352 tiles, 8.58 and 9.05; 64 of 704, 1536 tiles,
+// 15.05 and 15.26.
 bool use_side_streams(const Dims& d) {
-  return d.T * d.h >= (1L << 20) && d.T * d.h < (1L << 26);
+  if (d.T * d.h < (1L << 20)) return false;
+  if (d.T * d.h < (1L << 26)) return true;
+  return d.E > 0 && d.E * ((2 * d.fe + 255) / 256) * ((d.h + 255) / 256) < 2560;
 }
 
 hipError_t side_lane(SideLane** out) {
@@ -521,7 +530,7 @@ struct OptPlan {
 
 hipError_t opt_update(OptPlan* P, hipStream_t s, hipStream_t ws, const forge_adamw_tensor& t,
                       const float* grad, long n) {
-  hipStream_t os = s;  // without a lane (small layer): in order on the caller's stream
+  hipStream_t os = s;  // without a lane (use_side_streams): in order on the caller's stream
   if (P->lane) {
     if (P->next_ev + 2 > kLaneEvents) return hipErrorInvalidValue;
     os = P->lane->opt;

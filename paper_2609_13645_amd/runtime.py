@@ -351,8 +351,14 @@ def uses_side_streams(cfg: dict) -> bool:
     own streams: from 2^20 token x hidden elements (below, the event
     hand-offs cost more than the overlap gains, and one AdamW launch over
     all parameters beats one per weight) to 2^26 (from there on every product
-    fills the chip by itself)."""
-    return (1 << 20) <= cfg["batch"] * cfg["seq"] * cfg["hidden"] < (1 << 26)
+    of a dense layer fills the chip by itself, and the expert weight gradients
+    of a routed one where they have ten rounds of 256 x 256 tiles)."""
+    h = cfg["hidden"]
+    n = cfg["batch"] * cfg["seq"] * h
+    if n < 1 << 26:
+        return n >= 1 << 20
+    E = cfg.get("n_experts", 0)
+    return E > 0 and E * -(-2 * cfg["expert_ffn"] // 256) * -(-h // 256) < 2560
 
 
 class _PrefixedFlat:

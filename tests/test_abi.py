@@ -313,3 +313,14 @@ def test_attention_backward_partials_are_bounded():
 def test_side_streams_between_small_and_chip_filling_layers(tokens, hidden, side):
     from paper_2609_13645_amd import runtime
     assert runtime.uses_side_streams(dict(batch=1, seq=tokens, hidden=hidden)) is side
+
+
+@pytest.mark.parametrize("tokens,hidden,E,fe,side", [
+    (32768, 2048, 64, 1408, False), (32768, 2048, 8, 5632, False), (32768, 2048, 8, 1408, True),
+    (65536, 1024, 8, 1408, True), (65536, 1024, 64, 704, True), (8192, 2048, 64, 1408, True),
+    (256, 256, 8, 128, False)])
+def test_side_streams_of_routed_layers(tokens, hidden, E, fe, side):
+    """Few expert weight-gradient tiles leave the chip to be filled at any size."""
+    from paper_2609_13645_amd import runtime
+    cfg = dict(batch=1, seq=tokens, hidden=hidden, n_experts=E, top_k=2, expert_ffn=fe)
+    assert runtime.uses_side_streams(cfg) is side
