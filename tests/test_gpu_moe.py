@@ -42,14 +42,20 @@ def gpu_route(l32, k):
 
 @pytest.mark.parametrize("T,E,k,ties", [(8192, 64, 8, True), (37, 8, 3, True), (1000, 16, 16, False),
                                         (5, 64, 1, False), (4096, 160, 16, True),
-                                        (77, 256, 5, True), (130, 72, 9, False)])
+                                        (77, 256, 5, True), (130, 72, 9, False),
+                                        # expert counts around a lane's slots and the sort's
+                                        # groups, more than 64 choices (stored 64 at a time)
+                                        (33, 3, 3, False), (65, 100, 64, True), (257, 250, 65, True),
+                                        (70, 256, 256, True), (41, 193, 128, True), (1, 65, 2, False),
+                                        # more tokens than 512 sort blocks of 128
+                                        (65536, 8, 2, True), (65537, 8, 2, True), (140000, 72, 3, True)])
 def test_route_bit_exact(T, E, k, ties):
     banner(f"moe route T={T} E={E} k={k}")
     l32 = fi.router_logits(T, E, seed=5 + T)
     if ties:   # exact ties inside and at the top-k boundary
         l32[:, 3] = l32[:, 7 % E]
         l32[::3, 1] = l32[::3, 0]
-        l32[5] = 0.25
+        l32[5 % T] = 0.25
     got = gpu_route(l32, k)
     idx, gates, p, counts, offsets, perm = omoe.route(l32, k)
     assert np.array_equal(got[0], idx)
@@ -232,7 +238,7 @@ def test_route_nan_logits_stay_in_range():
 
 def test_moe_layer_160_experts_top16():
     # the expert count and top-k of the paper's 16B-A3B sparse model (App. B,
-    # 160 routed experts, top-16): four experts per routing lane, eight id bits
+    # 160 routed experts, top-16): three experts per routing lane, eight id bits
     cfg = fi.config("tiny", batch=1, seq=384, ffn=0, n_experts=160, top_k=16, expert_ffn=64,
                     aux_coef=0.01, seed=71)
     banner("moe layer 160 experts top-16")
